@@ -611,10 +611,10 @@ def main():
         ms_t = e0.elapsed_time(e1) / 3
         npts = float(np.prod(grid_dims))
         # algorithmic bytes per grid point: the field read once (8) and six components written (48);
-        # the implementation moves 600 per point (real->complex 24, forward FFT 3 x 32, per
-        # component pair the multiply 32, the inverse FFT 3 x 32 and the unpack 32)
+        # the implementation moves 256 per point (half-complex lines: rows and y forward 16 each, x
+        # forward and back to three fields 32, y and rows back 16 per component each)
         abytes = npts * (8 + 6 * 8)
-        ibytes = npts * (24 + 3 * 32 + 3 * (32 + 3 * 32 + 32))
+        ibytes = npts * (16 + 16 + 32 + 6 * 16 + 6 * 16)
         out["grid_tensor"] = {"ms": ms_t, "grid": list(grid_dims), "points_per_s": npts / (ms_t * 1e-3),
                               "algorithmic_GB_per_s": abytes / (ms_t * 1e-3) / 1e9,
                               "implementation_GB_per_s": ibytes / (ms_t * 1e-3) / 1e9}

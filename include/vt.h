@@ -237,7 +237,8 @@ vt_status vt_grid_sample(vt_ctx *ctx, const double *value, int32_t nx, int32_t n
  *   out    device, 6 x nx*ny*nz doubles: components xx, yy, zz, xy, xz, yz,
  *          each laid out like grid; overwritten.
  * nx, ny, nz are powers of two from 2 to 4096.  Periodic single-item contexts
- * only.  Scratch: 32 bytes per grid point, kept by the context.
+ * only.  Scratch: at most 96 / nz bytes per grid point (48 / nz if nz = 2), kept
+ * by the context.
  * Errors: VT_ERR_STATE, VT_ERR_ARG (sizes, kind, context), VT_ERR_OOM,
  * VT_ERR_HIP.
  */
@@ -250,10 +251,9 @@ vt_status vt_grid_tensor(vt_ctx *ctx, const double *grid, int32_t nx, int32_t ny
 /*
  * vt_grid_tensor_noalloc -- vt_grid_tensor for callers that cannot allocate
  * device memory (code under HIP graph capture, tight serving loops, harnesses
- * that forbid hipMalloc): the same result, bit for bit, with the 32 bytes per
- * grid point of FFT scratch taken from a static device array of the library
- * instead of the context.  The array holds VT_NOALLOC_TENSOR_POINTS points; each
- * device the library runs this on keeps its own copy (64 MiB) until the process
+ * that forbid hipMalloc): the same result, bit for bit, with the FFT scratch
+ * taken from a static device array of the library instead of the context.  The
+ * array serves grids of up to VT_NOALLOC_TENSOR_POINTS points; each device the library runs this on keeps its own copy (64 MiB) until the process
  * ends.  The call allocates nothing (no hipMalloc, hipFree or allocating
  * library routine).  Every call on one device shares that device's array, so
  * calls that overlap on one device (different streams, or different host

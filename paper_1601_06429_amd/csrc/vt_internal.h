@@ -159,7 +159,7 @@ struct vt_ctx {
     uint8_t *smark = nullptr;
     int32_t *squeue = nullptr;
     int64_t cap_struct = 0;
-    // grid tensors (spectral.hip): two complex work arrays of the grid's size
+    // grid tensors (spectral.hip): planes of Nyquist values (complex)
     void *spec_buf = nullptr;
     int64_t cap_spec = 0;
     // optional stage timing
