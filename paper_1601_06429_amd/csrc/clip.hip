@@ -243,32 +243,31 @@ __device__ __forceinline__ void clip_cells(const ClipArgs &A) {
     const int wid = threadIdx.x >> 6;
     M &S = *reinterpret_cast<M *>(smem + (size_t)wid * sizeof(M));
     const int lane = lane_id();
-    const uint64_t lt = lanemask_lt();
-    const uint64_t mybit = 1ull << lane;
 
     const int64_t ntodo = RETRY ? (int64_t)min((uint64_t)A.counters[CTR_QUEUE], (uint64_t)A.queue_cap) : A.ncells;
     // Work distribution.  The large kernel (and the one-queue mapping) hands out cells from one
     // counter.  With XCD segments, the cells (in Morton order) are cut into nseg contiguous
     // segments; a wavefront of workgroup b starts on segment b % nseg, the XCD its workgroup runs
     // on, so each XCD's L2 serves one compact region, and when that segment is exhausted the
-    // wavefront moves to the next one, until it has found all nseg exhausted.  Every counter only
-    // grows and a segment is left only once exhausted, so every cell is taken exactly once and
-    // every wavefront exits after at most nseg exhausted segments.
+    // wavefront moves to the next one that still has cells, which one load of all counters tells
+    // (an atomic on each of them in turn costs a wavefront eight round trips before it may exit).
+    // Every counter only grows and a segment is left only once exhausted, so every cell is taken
+    // exactly once and every wavefront exits once it finds all segments exhausted.
     const int nseg = RETRY ? 1 : A.xcd_segments;
     int seg = RETRY ? 0 : (int)(blockIdx.x % (unsigned)nseg);
-    int left = nseg;
 
     for (;;) {
         const int64_t s_lo = RETRY ? 0 : ntodo * seg / nseg, s_hi = RETRY ? ntodo : ntodo * (seg + 1) / nseg;
         int64_t w = 0;
         if (lane == 0) {
-            uint32_t *ctr = RETRY ? &A.counters[CTR_RETRY] : nseg == 1 ? &A.counters[CTR_CELL] : &A.counters[CTR_SEG0 + seg];
+            uint32_t *ctr = RETRY ? &A.counters[CTR_RETRY] : nseg == 1 ? &A.counters[CTR_CELL] : &A.counters[CTR_SEG(seg)];
             w = (int64_t)atomicAdd(ctr, 1u);
         }
         w = (int64_t)uni_i((int)__shfl((long long)w, 0)) + s_lo;
         if (w >= s_hi) {
-            if (--left == 0) break;
-            seg = seg + 1 == nseg ? 0 : seg + 1;
+            if (nseg == 1) break;
+            seg = next_segment(A.counters, ntodo, seg);
+            if (seg < 0) break;
             continue;
         }
         const int32_t cslot = uni_i(RETRY ? A.queue[w] : (int32_t)w);
@@ -331,7 +330,7 @@ __device__ __forceinline__ void clip_cells(const ClipArgs &A) {
         auto stage_search = [&]() {
 #pragma unroll
             for (int s = 0; s < VPL; ++s)
-                if (P.alive[s] & mybit) {
+                if (in_mask(P.alive[s])) {
                     const double x = (double)P.vx[s], y = (double)P.vy[s], z = (double)P.vz[s];
                     S.u.s.vp[s * 64 + lane][0] = x;
                     S.u.s.vp[s * 64 + lane][1] = y;
@@ -389,7 +388,7 @@ __device__ __forceinline__ void clip_cells(const ClipArgs &A) {
             for (int s_ = 0; s_ < VPL; ++s_) {
                 farv[s_] = P.alive[s_];
                 if (prune)
-                    farv[s_] = __ballot((P.alive[s_] & mybit) && 2.0 * S.u.s.vr[s_ * 64 + lane] * (1.0 + 1e-7) >= rmin);
+                    farv[s_] = __ballot(in_mask(P.alive[s_]) && 2.0 * S.u.s.vr[s_ * 64 + lane] * (1.0 + 1e-7) >= rmin);
             }
             for (int base = 0; base < nbox; base += WAVE) {
                 const int k = base + lane;
@@ -477,7 +476,7 @@ __device__ __forceinline__ void clip_cells(const ClipArgs &A) {
                 }
                 const uint64_t km = __ballot(keep);
                 if (keep) {
-                    const int slot = count + __popcll(km & lt);
+                    const int slot = count + rank_in(km);
                     S.rb[slot] = b;
                     S.rp[slot] = e - b;  // length for now
                 }
@@ -554,7 +553,7 @@ __device__ __forceinline__ void clip_cells(const ClipArgs &A) {
                 uint64_t farv[VPL];
 #pragma unroll
                 for (int s_ = 0; s_ < VPL; ++s_)
-                    farv[s_] = __ballot((P.alive[s_] & mybit) && 2.0 * S.u.s.vr[s_ * 64 + lane] * (1.0 + 1e-7) >= rmin);
+                    farv[s_] = __ballot(in_mask(P.alive[s_]) && 2.0 * S.u.s.vr[s_ * 64 + lane] * (1.0 + 1e-7) >= rmin);
                 // box u at level l (unwrapped coordinates): does it meet the shell and is it reached
                 // by a vertex's empty sphere?  dmin2: its squared distance from the seed
                 auto box_test = [&](int l, const int u[3], double &dmin2) -> bool {
@@ -621,7 +620,7 @@ __device__ __forceinline__ void clip_cells(const ClipArgs &A) {
                     }
                     const uint64_t km = __ballot(keep);
                     if (keep) {
-                        const int slot = ncur + __popcll(km & lt);
+                        const int slot = ncur + rank_in(km);
                         S.fine.pk[0][slot] = pack_box(u, lvl);
                         S.fine.b[0][slot] = b;
                         S.fine.n[0][slot] = e - b;
@@ -669,7 +668,7 @@ __device__ __forceinline__ void clip_cells(const ClipArgs &A) {
                         split_any |= __ballot(split) != 0;
                         const uint64_t km = __ballot(keep);
                         if (keep) {
-                            const int slot = nnext + __popcll(km & lt);
+                            const int slot = nnext + rank_in(km);
                             S.fine.pk[cur ^ 1][slot] = pk;
                             S.fine.b[cur ^ 1][slot] = b;
                             S.fine.n[cur ^ 1][slot] = len;
@@ -814,7 +813,7 @@ __device__ __forceinline__ void clip_cells(const ClipArgs &A) {
 #pragma unroll
                 for (int s = 0; s < VPL; ++s) {
                     bool rel = false;
-                    if (P.alive[s] & mybit) {
+                    if (in_mask(P.alive[s])) {
                         const double x = (double)P.vx[s], y = (double)P.vy[s], z = (double)P.vz[s];
                         const double ex = fmax(0.0, fmax(bx0 - x, x - bx1));
                         const double ey = fmax(0.0, fmax(by0 - y, y - by1));
@@ -846,9 +845,9 @@ __device__ __forceinline__ void clip_cells(const ClipArgs &A) {
                 }
                 uint64_t am = __ballot(keep && act);
                 while (am) {
-                    const double key = (am & mybit) ? d2 : 1e300;
+                    const double key = in_mask(am) ? d2 : 1e300;
                     const double mn = wave_min_x(key);
-                    const uint64_t who = __ballot((am & mybit) && d2 == mn);
+                    const uint64_t who = __ballot(in_mask(am) && d2 == mn);
                     const int k = uni_i(__builtin_ctzll(who));
                     am &= ~(1ull << k);
                     P4<double> p64;
@@ -923,7 +922,7 @@ __device__ __forceinline__ void clip_cells(const ClipArgs &A) {
                 }
                 const uint64_t km = __ballot(keep);
                 if (keep) {
-                    const int slot = n + __popcll(km & lt);
+                    const int slot = n + rank_in(km);
                     if (slot < VT_CAND_MAX) {
                         S.u.c.cd[slot][0] = dx;
                         S.u.c.cd[slot][1] = dy;
@@ -1003,7 +1002,7 @@ __device__ __forceinline__ void clip_cells(const ClipArgs &A) {
 #pragma unroll
                         for (int s = 0; s < VPL; ++s) {
                             bool f = false;
-                            if (P.alive[s] & mybit) {
+                            if (in_mask(P.alive[s])) {
                                 S.P.st[s * 64 + lane][0] = P.vx[s];
                                 S.P.st[s * 64 + lane][1] = P.vy[s];
                                 S.P.st[s * 64 + lane][2] = P.vz[s];
@@ -1021,7 +1020,7 @@ __device__ __forceinline__ void clip_cells(const ClipArgs &A) {
                         }
                         wave_sync();
                         bool act = false;
-                        if (pend & mybit) {
+                        if (in_mask(pend)) {
                             const int slot = (int)(key & 0xFFu);
                             const double dx = S.u.c.cd[slot][0], dy = S.u.c.cd[slot][1], dz = S.u.c.cd[slot][2];
                             const double d2 = dx * dx + dy * dy + dz * dz;
@@ -1052,7 +1051,7 @@ __device__ __forceinline__ void clip_cells(const ClipArgs &A) {
                                 }
                             }
                         }
-                        uint64_t am = __ballot((pend & mybit) && act);
+                        uint64_t am = __ballot(in_mask(pend) && act);
                         pend = 0;
                         int cuts = 0;
                         while (am) {
@@ -1151,7 +1150,7 @@ __device__ __forceinline__ void clip_cells(const ClipArgs &A) {
         double r2max = 0.0;
 #pragma unroll
         for (int s = 0; s < VPL; ++s) {
-            if (P.alive[s] & mybit) {
+            if (in_mask(P.alive[s])) {
                 double x, y, z;
                 P.pos64(S.P, s, x, y, z);
                 S.u.f.vp[s * 64 + lane][0] = x;
@@ -1165,7 +1164,7 @@ __device__ __forceinline__ void clip_cells(const ClipArgs &A) {
         int32_t tag_l = -1;
         uint32_t gid_l = 0;
         if constexpr (VPL == 1) {
-            if (P.fa[0] & mybit) {
+            if (in_mask(P.fa[0])) {
                 tag_l = S.P.ptag[lane];
                 if (tag_l >= 0) gid_l = (uint32_t)A.sgid[tag_l];
             }
@@ -1178,7 +1177,7 @@ __device__ __forceinline__ void clip_cells(const ClipArgs &A) {
         for (int r = 0; r < VPL; ++r) {
             area_l[r] = 0.0;
             const int f = r * 64 + lane;
-            if (!(P.fa[r] & mybit)) continue;
+            if (!in_mask(P.fa[r])) continue;
             uint64_t mf[VPL];
             int i0 = -1;
 #pragma unroll
@@ -1261,7 +1260,7 @@ __device__ __forceinline__ void clip_cells(const ClipArgs &A) {
             // each face lane holds its facet; its row is the rank of its key (global id, then slot)
             // among the kept facets, counted over their keys read lane by lane
             keys[0] = ~0ull;
-            if ((P.fa[0] & mybit) && area_l[0] > amin) {
+            if (in_mask(P.fa[0]) && area_l[0] > amin) {
                 if (tag_l < 0) wall |= 1u << ((-1 - tag_l) & 7);
                 else keys[0] = ((uint64_t)gid_l << 9) | (uint64_t)lane;
             }
@@ -1288,7 +1287,7 @@ __device__ __forceinline__ void clip_cells(const ClipArgs &A) {
             for (int r = 0; r < VPL; ++r) {
                 const int f = r * 64 + lane;
                 keys[r] = ~0ull;
-                if ((P.fa[r] & mybit) && area_l[r] > amin) {
+                if (in_mask(P.fa[r]) && area_l[r] > amin) {
                     int32_t tag = S.P.ptag[f];
                     if (tag < 0) wall |= 1u << ((-1 - tag) & 7);
                     else keys[r] = ((uint64_t)(uint32_t)A.sgid[tag] << 9) | (uint64_t)f;
@@ -1326,12 +1325,12 @@ __device__ __forceinline__ void clip_cells(const ClipArgs &A) {
             const int nf = __popcll(fam);
             if (nf <= VT_TOPO_FACES) {
                 const int64_t tb = (int64_t)cslot * VT_TOPO_STRIDE;
-                if (fam & mybit) A.ctopo[tb + __popcll(fam & lt)] = S.P.ptag[lane];
-                if (P.alive[0] & mybit) {
+                if (in_mask(fam)) A.ctopo[tb + rank_in(fam)] = S.P.ptag[lane];
+                if (in_mask(P.alive[0])) {
                     const uint32_t t = P.vt[0];
                     auto rk = [&](uint32_t f) -> uint32_t { return (uint32_t)__popcll(fam & ((1ull << (f & 63u)) - 1ull)); };
                     const uint32_t tr = rk(t & 0xFFu) | (rk((t >> 8) & 0xFFu) << 8) | (rk((t >> 16) & 0xFFu) << 16);
-                    A.ctopo[tb + VT_TOPO_FACES + __popcll(P.alive[0] & lt)] = (int32_t)tr;
+                    A.ctopo[tb + VT_TOPO_FACES + rank_in(P.alive[0])] = (int32_t)tr;
                 }
                 nf_rec = nf;
             }
@@ -1371,7 +1370,7 @@ __device__ __forceinline__ void clip_cells(const ClipArgs &A) {
             A.cnv[cslot] = nvert;
             A.cnf[cslot] = nf_rec;
             A.cnt[cslot] = ntested;
-            atomicAdd((unsigned long long *)&A.counters[CTR_NNZ_LO], (unsigned long long)kept);
+            atomicAdd((unsigned long long *)&A.counters[CTR_SEG_NNZ(seg)], (unsigned long long)kept);
         }
     }
 }
@@ -1392,7 +1391,6 @@ __global__ void __launch_bounds__(256) k_planes(ClipArgs A, int32_t *out) {
     __shared__ PlanesMem SM[4];
     PlanesMem &S = SM[threadIdx.x >> 6];
     const int lane = lane_id();
-    const uint64_t lt = lanemask_lt();
     const int64_t nw = (int64_t)gridDim.x * 4;
     for (int64_t c = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); c < A.ncells; c += nw) {
         const uint8_t st = A.cstat[c];
@@ -1471,7 +1469,7 @@ __global__ void __launch_bounds__(256) k_planes(ClipArgs A, int32_t *out) {
             }
             const uint64_t pm = __ballot(part);
             if (part) {
-                const int slot = npart + __popcll(pm & lt);
+                const int slot = npart + rank_in(pm);
                 S.rb[slot] = b;
                 S.rp[slot] = e - b;
             }

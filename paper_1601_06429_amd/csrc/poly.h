@@ -33,6 +33,14 @@ __device__ __forceinline__ uint64_t lanemask_lt() {
     return l == 0 ? 0ull : (~0ull >> (64 - l));
 }
 
+// Bit masks over the lanes are kept in scalar registers: whether this lane's bit is set costs no
+// instruction of its own (the mask is and-ed to exec), and the bits below this lane are counted
+// without a mask of them in vector registers.
+__device__ __forceinline__ bool in_mask(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+__device__ __forceinline__ int rank_in(uint64_t m) {
+    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
 // orders LDS accesses of the lanes of one wavefront
 __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -252,16 +260,34 @@ __device__ __forceinline__ DevItem uniform_item(const DevItem &g) {
     return it;
 }
 
-// exclusive prefix sum over the wave
+// exclusive prefix sum over the wave, its steps DPP moves (shifts within rows of 16 lanes, then the
+// last lane of a row broadcast to the next row, and lane 31 to the upper half)
 __device__ __forceinline__ int wave_excl_scan(int v, int *total) {
-    int l = lane_id();
     int x = v;
-    for (int o = 1; o < 64; o <<= 1) {
-        int y = __shfl_up(x, o);
-        if (l >= o) x += y;
-    }
-    *total = __shfl(x, 63);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, false);  // row_shr:1
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, false);  // row_shr:2
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, false);  // row_shr:4
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, false);  // row_shr:8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);  // row_bcast:15 into rows 1 and 3
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);  // row_bcast:31 into rows 2 and 3
+    *total = __builtin_amdgcn_readlane(x, 63);
     return x - v;
+}
+
+// The next XCD segment after `sg` (cyclically) whose counter has not passed its last cell, -1 if
+// none has cells left: one load of the counters by the lanes.  A counter only grows, so a segment
+// found drained stays so.
+__device__ __forceinline__ int next_segment(const uint32_t *counters, int64_t ncells, int sg) {
+    const int l = lane_id();
+    bool open = false;
+    if (l < VT_XCD_SEGMENTS) {
+        const uint32_t t = __hip_atomic_load(&counters[CTR_SEG(l)], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        open = ncells * l / VT_XCD_SEGMENTS + (int64_t)t < ncells * (l + 1) / VT_XCD_SEGMENTS;
+    }
+    const uint64_t m = __ballot(open);
+    if (m == 0ull) return -1;
+    const uint64_t after = m & ~((2ull << sg) - 1ull);
+    return uni_i(__builtin_ctzll(after ? after : m));
 }
 
 // bitonic sort of 64 keys (one per lane), ascending by lane
@@ -489,11 +515,10 @@ struct Poly {
     }
 
     __device__ void update_r2() {
-        const uint64_t mybit = 1ull << lane_id();
         double r2l = 0.0;
 #pragma unroll
         for (int s = 0; s < VPL; ++s) {
-            if (alive[s] & mybit) {
+            if (in_mask(alive[s])) {
                 double x = (double)vx[s], y = (double)vy[s], z = (double)vz[s];
                 double d = x * x + y * y + z * z;
                 if constexpr (MIXED) {
@@ -509,8 +534,6 @@ struct Poly {
     // Clip by {y : p.y <= p.d} (p64 in FP64); `tag` identifies the plane.
     __device__ int clip(Mem &S, const P4<double> &p64, int32_t tag) {
         const int lane = lane_id();
-        const uint64_t lt = lanemask_lt();
-        const uint64_t mybit = 1ull << lane;
         P4<T> p;
         p.x = (T)p64.x;
         p.y = (T)p64.y;
@@ -527,7 +550,7 @@ struct Poly {
         bool any = false, all = true;
 #pragma unroll
         for (int s = 0; s < VPL; ++s) {
-            bool al = (alive[s] & mybit) != 0;
+            bool al = in_mask(alive[s]);
             T sv = side<T>(vx[s], vy[s], vz[s], p);
             bool o = sv > T(0);
             if constexpr (MIXED) {
@@ -578,7 +601,7 @@ struct Poly {
 #pragma unroll
                     for (int ww = 0; ww < VPL; ++ww) {
                         uint64_t x = (e == 0) ? (m0[ww] & m1[ww]) : (e == 1) ? (m1[ww] & m2[ww]) : (m2[ww] & m0[ww]);
-                        if (ww == s) x &= ~mybit;
+                        if (ww == s) x &= ~(1ull << lane);
                         nonzero |= x != 0;
                         if (x & Mk[ww]) keptTwin = false;
                     }
@@ -596,7 +619,7 @@ struct Poly {
 #pragma unroll
         for (int s = 0; s < VPL; ++s) {
             uint64_t b1 = __ballot(nbv[s] & 1), b2 = __ballot(nbv[s] & 2);
-            pre_s[s] = NB + __popcll(b1 & lt) + 2 * __popcll(b2 & lt);
+            pre_s[s] = NB + rank_in(b1) + 2 * rank_in(b2);
             NB += __popcll(b1) + 2 * __popcll(b2);
         }
         int nfree = 0;
@@ -621,7 +644,7 @@ struct Poly {
         for (int r = 0; r < VPL; ++r) {
             const int f = r * 64 + lane;
             bool kept = false;
-            if (fa[r] & mybit) {
+            if (in_mask(fa[r])) {
 #pragma unroll
                 for (int ww = 0; ww < VPL; ++ww) {
                     const uint64_t m = S.fm[f][ww] & ~Mk[ww];
@@ -650,8 +673,8 @@ struct Poly {
 #pragma unroll
         for (int s = 0; s < VPL; ++s) {
             const uint64_t F = ~alive[s] | Mk[s];
-            const int r = rank0 + __popcll(F & lt);
-            const bool got = ((F & mybit) != 0) && r < NB;
+            const int r = rank0 + rank_in(F);
+            const bool got = in_mask(F) && r < NB;
             if (got) {
                 const uint32_t t = S.stt[r];
                 const int fa_ = t & 0xFF, fb_ = (t >> 8) & 0xFF;
@@ -672,8 +695,8 @@ struct Poly {
                 vy[s] = wy;
                 vz[s] = wz;
                 vt[s] = t;
-                atomicOr((unsigned long long *)&S.fm[fa_][s], (unsigned long long)mybit);
-                atomicOr((unsigned long long *)&S.fm[fb_][s], (unsigned long long)mybit);
+                atomicOr((unsigned long long *)&S.fm[fa_][s], 1ull << lane);
+                atomicOr((unsigned long long *)&S.fm[fb_][s], 1ull << lane);
             }
             const uint64_t nm = __ballot(got);
             alive[s] = (alive[s] & ~Mk[s]) | nm;
@@ -717,7 +740,7 @@ struct Poly {
         const uint64_t mybit = 1ull << lane;
 #pragma unroll
         for (int s = 0; s < VPL; ++s) {
-            if (alive[s] & mybit) {
+            if (in_mask(alive[s])) {
                 double x, y, z;
                 pos64(S, s, x, y, z);
                 vp[s * 64 + lane][0] = x;
@@ -729,7 +752,7 @@ struct Poly {
         double acc = 0.0;
 #pragma unroll
         for (int s = 0; s < VPL; ++s) {
-            if (!(alive[s] & mybit)) continue;
+            if (!in_mask(alive[s])) continue;
             const int u = s * 64 + lane;
             const uint32_t t = vt[s];
             const int f[3] = {(int)(t & 0xFF), (int)((t >> 8) & 0xFF), (int)((t >> 16) & 0xFF)};

@@ -397,7 +397,11 @@ vt_status vt_query(vt_ctx *c, int64_t *nnz, int64_t *n_retried, int64_t *n_incom
     TRY(hipStreamSynchronize(c->stream));
     TRY(hipMemcpy(c->h_counters, c->counters, sizeof(uint32_t) * CTR_COUNT, hipMemcpyDeviceToHost));
     const uint32_t *h = c->h_counters;
-    if (nnz) *nnz = (int64_t)(((uint64_t)h[CTR_NNZ_HI] << 32) | h[CTR_NNZ_LO]);
+    if (nnz) {
+        *nnz = 0;
+        for (int k = 0; k < VT_XCD_SEGMENTS; ++k)
+            *nnz += (int64_t)(((uint64_t)h[CTR_SEG_NNZ(k) + 1] << 32) | h[CTR_SEG_NNZ(k)]);
+    }
     if (n_retried) *n_retried = h[CTR_QUEUE];
     if (n_incomplete) *n_incomplete = h[CTR_INCOMPLETE];
     uint32_t st = h[CTR_STATUS];
