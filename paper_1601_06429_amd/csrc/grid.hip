@@ -18,10 +18,24 @@
 // lane keeps O(1) state.  Work items (face, rectangle, plane) are spread over
 // the lanes of the wavefront that rebuilt the cell from its facets.
 //
+// A face lies between two cells and its integrals serve both, with opposite signs: one of the two
+// cells, known to both from their lowest x voxels, takes them with the difference of the weights
+// (value / voxel volume).  The kernel is bound by VALU issue at two wavefronts per SIMD (237 vector
+// registers, 19 KB of LDS each), so halving the integrals, the face loops and the classification is
+// what counts: 2M cells on 256^3 took 29.5 ms with every face integrated from both sides and take
+// 22.4 ms now (region integrals 9.0, classifying and emitting 5.1, face loops 2.9, choosing the
+// faces and the cell's extent 2.0, rebuilding 2.3, dealing cells 0.7, by copies that leave steps
+// out); 5003 cells on 41 x 29 x 50, 0.67 -> 0.13 ms, most of it from taking one cell at a time
+// instead of 16 where 16 leave wavefronts without work.
+//
 // The grid lines are evaluated at X_i + 1e-12 h (likewise in y and z): a
 // vertex or face exactly on a grid line (lattice inputs) then has no tie; the
 // overlap volumes move by at most 1e-12 of a voxel.
+#include <algorithm>
+
 #include "rebuild.h"
+
+#define GRID_BATCH 16  // cells a wavefront takes at a time on large inputs
 
 template <int VPL>
 struct GridMem {
@@ -37,8 +51,9 @@ struct GridMem {
     int32_t fpl[FMAX][2];    // planes strictly inside the face's x range: m0, count
     int32_t ipre[FMAX + 1];  // prefix of work items per face
     int32_t fid[FMAX];       // compacted face slots
-    uint64_t iq[2][128];     // work items queued for integration (face, plane, rectangle offsets):
-                             // [0] the faces' lowest planes (pi == 0), [1] planes that cut a face
+    int32_t flow[FMAX];      // the neighbour's lowest x voxel (this cell's frame): its weight counts from there up
+    double fw[FMAX];         // this cell's weight less the neighbour's
+    uint64_t iq[128];        // work items queued for integration (face, plane, rectangle offsets)
     double acc[ACC];         // the cell's contributions per voxel of its box
     PolyMem<double, VPL> P;
 };
@@ -62,8 +77,10 @@ struct GridArgs {
     const int32_t *cnv;
     int64_t npos;             // sorted particles (bound of a record's face tags)
     const int32_t *stage_ids;
-    const int32_t *srow;
-    const double *value;
+    const double *gval;       // per sorted particle: its cell's weight value / voxel volume, 0 if it takes no part
+    const int32_t *glow;      // its cell's lowest x voxel
+    int share;                // faces between two cells are integrated once, for both
+    int batch;                // cells a wavefront takes at a time (at most GRID_BATCH)
     uint32_t *counters;
     double *grid;
     int nx, ny, nz;
@@ -157,14 +174,14 @@ __device__ __forceinline__ void slab(double a, double b, double ib, double lo, d
 
 // D = Omega ∩ R ∩ H in coordinates relative to R's corner (Y0, Z0): Omega the
 // counter-clockwise loop lp[o .. o+m) of seed-relative vertices,
-// R = [Y0, Y0 + hy] x [Z0, Z0 + hz], H = {hs (e - ny y - nz z) > 0} if useH (the
+// R = [Y0, Y0 + hy] x [Z0, Z0 + hz], H = {hs (e - ny y - nz z) > 0} (the
 // part of the face above x = X), with e given for the shifted coordinates and
 // rnx = 1 / n_x.  One pass over Omega's edges clips each edge to R ∩ H and, for
 // every edge, restricts R's four edges and the chord to its inner side; those
 // segments are integrated after the pass.
-template <int VPL, bool useH>
+template <int VPL>
 __device__ __forceinline__ Reg region_integrals(const GridMem<VPL> &S, int o, int m, double Y0, double Z0, double hy, double hz,
-                                double hs, double e, double ny, double nz, double X, double rnx) {
+                                double ihy, double ihz, double hs, double e, double ny, double nz, double X, double rnx) {
     Reg D = {0.0, 0.0};
     auto gH = [&](double y, double z) { return hs * (e - ny * y - nz * z); };
     const double Oy = S.lp[o][1] - Y0, Oz = S.lp[o][2] - Z0, gO = S.lp[o][0] - X;
@@ -180,7 +197,7 @@ __device__ __forceinline__ Reg region_integrals(const GridMem<VPL> &S, int o, in
     // the chord x = X: a segment through the point of the line nearest R's centre, long
     // enough to cross R, directed with H on its left (x - X = 0 on it), clipped to R
     double cy0 = 0.0, cz0 = 0.0, cy1 = 0.0, cz1 = 0.0, ct0 = 0.0, ct1 = 0.0;
-    if constexpr (useH) {
+    {
         const double nn = ny * ny + nz * nz;
         const double cy = 0.5 * hy, cz = 0.5 * hz;
         const double sft = (ny * cy + nz * cz - e) / nn;
@@ -200,8 +217,7 @@ __device__ __forceinline__ Reg region_integrals(const GridMem<VPL> &S, int o, in
     // right and downwards on the left; crossing y = c rightwards bounds it from below and
     // leftwards from above.  A line that no edge crosses misses Omega.  Edge r of R runs from
     // corner r to corner r + 1 (counter-clockwise), t along it.
-    const double ihy = 1.0 / hy, ihz = 1.0 / hz;
-    int crossed[4] = {0, 0, 0, 0};
+    unsigned crossed = 0;  // bit r: an edge of Omega crosses the line of R's edge r
     double y0 = Oy, z0 = Oz, xa = gO;
     for (int k = 0; k < m; ++k) {
         const int k1 = (k + 1 == m) ? 0 : k + 1;
@@ -213,7 +229,7 @@ __device__ __forceinline__ Reg region_integrals(const GridMem<VPL> &S, int o, in
             double t0 = 0.0, t1 = 1.0;
             slab(y0, dy, iby, 0.0, hy, t0, t1);
             slab(z0, dz, ibz, 0.0, hz, t0, t1);
-            if constexpr (useH) cyrus_beck(gH(y0, z0), gH(y1, z1), t0, t1);
+            cyrus_beck(gH(y0, z0), gH(y1, z1), t0, t1);
             if (t0 < t1) tri(y0 + t0 * dy, z0 + t0 * dz, xa + t0 * dx, y0 + t1 * dy, z0 + t1 * dz, xa + t1 * dx);
         }
         // (b) crossings with z = 0 (edge 0, t = y / hy), y = hy (edge 1, t = z / hz),
@@ -235,28 +251,28 @@ __device__ __forceinline__ Reg region_integrals(const GridMem<VPL> &S, int o, in
             rt1[1] = lf1 ? fmin(rt1[1], zc1) : rt1[1];
             rt1[3] = rt3 ? fmin(rt1[3], zc3) : rt1[3];
             rt0[3] = lf3 ? fmax(rt0[3], zc3) : rt0[3];
-            crossed[0] |= (up0 || dn0) ? 1 : 0;
-            crossed[1] |= (rt1_ || lf1) ? 1 : 0;
-            crossed[2] |= (up2 || dn2) ? 1 : 0;
-            crossed[3] |= (rt3 || lf3) ? 1 : 0;
+            crossed |= (up0 || dn0) ? 1u : 0u;
+            crossed |= (rt1_ || lf1) ? 2u : 0u;
+            crossed |= (up2 || dn2) ? 4u : 0u;
+            crossed |= (rt3 || lf3) ? 8u : 0u;
         }
         // (c) the chord restricted to the inner side of this edge
-        if constexpr (useH) cyrus_beck(dy * (cz0 - z0) - dz * (cy0 - y0), dy * (cz1 - z0) - dz * (cy1 - y0), ct0, ct1);
+        cyrus_beck(dy * (cz0 - z0) - dz * (cy0 - y0), dy * (cz1 - z0) - dz * (cy1 - y0), ct0, ct1);
         y0 = y1;
         z0 = z1;
         xa = xb;
     }
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        rt0[r] = crossed[r] ? rt0[r] : 1.0;
-        rt1[r] = crossed[r] ? rt1[r] : 0.0;
+        rt0[r] = (crossed >> r) & 1u ? rt0[r] : 1.0;
+        rt1[r] = (crossed >> r) & 1u ? rt1[r] : 0.0;
     }
     // (b) edges of R inside Omega ∩ H
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const double qy0 = ry[r], qz0 = rz[r], qy1 = ry[r + 1], qz1 = rz[r + 1];
         double t0 = rt0[r], t1 = rt1[r];
-        if constexpr (useH) cyrus_beck(gH(qy0, qz0), gH(qy1, qz1), t0, t1);
+        cyrus_beck(gH(qy0, qz0), gH(qy1, qz1), t0, t1);
         if (t0 < t1) {
             const double dy = qy1 - qy0, dz = qz1 - qz0;
             const double ya = qy0 + t0 * dy, za = qz0 + t0 * dz, yb = qy0 + t1 * dy, zb = qz0 + t1 * dz;
@@ -264,7 +280,7 @@ __device__ __forceinline__ Reg region_integrals(const GridMem<VPL> &S, int o, in
         }
     }
     // (c) the chord inside Omega ∩ R
-    if (useH && ct0 < ct1) {
+    if (ct0 < ct1) {
         const double ey = cy1 - cy0, ez = cz1 - cz0;
         tri(cy0 + ct0 * ey, cz0 + ct0 * ez, 0.0, cy0 + ct1 * ey, cz0 + ct1 * ez, 0.0);
     }
@@ -273,8 +289,7 @@ __device__ __forceinline__ Reg region_integrals(const GridMem<VPL> &S, int o, in
 
 // The deposit of one wavefront (wid its index in the block's LDS).  The large kernel
 // (RETRY) takes queued cells: seg 0 both queues, seg 1 the clip's retry queue only (counter
-// CTR_GRID_RETRY), seg 2 only the cells the normal kernel handed over (counter CTR_GRID, zeroed
-// after the normal kernel has run).
+// CTR_GRID_RETRY), seg 2 only the cells the normal kernel handed over (counter CTR_GRID).
 template <typename PT4, int VPL, bool RETRY>
 __device__ __forceinline__ void grid_body(const GridArgs &A, char *smem, int wid) {
     using M = GridMem<VPL>;
@@ -283,70 +298,71 @@ __device__ __forceinline__ void grid_body(const GridArgs &A, char *smem, int wid
     const uint64_t mybit = 1ull << lane;
     const uint64_t lt = lanemask_lt();
     const DevItem &it = A.items[0];
-    const double h[3] = {it.L[0] / A.nx, it.L[1] / A.ny, it.L[2] / A.nz};
-    const double ih[3] = {1.0 / h[0], 1.0 / h[1], 1.0 / h[2]};
+    // the same in every lane: in scalar registers, of which this kernel has more to spare
+    const double h[3] = {uni_d(it.L[0] / A.nx), uni_d(it.L[1] / A.ny), uni_d(it.L[2] / A.nz)};
+    const double ih[3] = {uni_d(1.0 / h[0]), uni_d(1.0 / h[1]), uni_d(1.0 / h[2])};
     const double del[3] = {1e-12 * h[0], 1e-12 * h[1], 1e-12 * h[2]};  // grid-line offset
-    const double hv = h[0] * h[1] * h[2];
     const int dims[3] = {A.nx, A.ny, A.nz};
     const int64_t nq = RETRY ? (int64_t)min((uint64_t)A.counters[CTR_QUEUE], (uint64_t)A.queue_cap) : 0;
+    // The normal kernel deals its cells as the clip kernel does: contiguous segments of the Morton
+    // order, one per XCD, each with its counter (one counter for all waves took 1.5 ms of atomics on
+    // one address at 2M), and a wavefront that finds its segment drained goes on to the next.
+    // When it is, one load of all counters names the segments that still have cells.
+    constexpr int nseg = RETRY ? 1 : VT_XCD_SEGMENTS;
+    int sg = RETRY ? 0 : (int)(blockIdx.x % (unsigned)nseg);
     int64_t w_lo = 0, ntodo = RETRY ? nq + (int64_t)min((uint64_t)A.counters[CTR_GRID_Q], (uint64_t)A.gqueue_cap)
                                     : A.ncells;
-    int ctr = RETRY ? CTR_GRID_RETRY : CTR_GRID;
+    int ctr = RETRY ? CTR_GRID_RETRY : CTR_SEG(sg);
     if (RETRY && A.seg == 1) ntodo = nq;
     if (RETRY && A.seg == 2) {
         w_lo = nq;
         ctr = CTR_GRID;
     }
 
-    // Cells are taken GB at a time: lane l loads the scalars of the batch's cell l (the latency
-    // of those dependent loads is paid once per batch), a cell inside one voxel (its ball of
-    // radius R, the largest vertex distance, is) deposits its whole volume from its lane, and
-    // the wave then rebuilds the other cells one after another.
-    constexpr int GB = 16;
+    // Cells are taken A.batch at a time: lane l loads the scalars of the batch's cell l (the latency
+    // of those dependent loads is paid once per batch), and the wave then rebuilds the cells that
+    // take part one after another.
+    const int gb = RETRY ? 1 : A.batch;
     for (;;) {
         int64_t wb = 0;
-        if (lane == 0) wb = (int64_t)atomicAdd(&A.counters[ctr], (uint32_t)GB);
+        if (lane == 0) wb = (int64_t)atomicAdd(&A.counters[ctr], (uint32_t)gb);
         wb = (int64_t)uni_i((int)__shfl((long long)wb, 0)) + w_lo;
-        if (wb >= ntodo) break;
+        if constexpr (!RETRY) {
+            wb += A.ncells * sg / nseg;
+            ntodo = A.ncells * (sg + 1) / nseg;
+            if (wb >= ntodo) {
+                sg = next_segment(A.counters, A.ncells, sg);
+                if (sg < 0) break;
+                ctr = CTR_SEG(sg);
+                continue;
+            }
+        } else if (wb >= ntodo) {
+            break;
+        }
         const int64_t wl = wb + lane;
-        int32_t cl = 0;
+        int32_t cl = 0, jl = 0, lowl = 0;
         double vl = 0.0, xl = 0.0, yl = 0.0, zl = 0.0;
-        bool todo = false;
-        if (lane < GB && wl < ntodo) {
+        if (lane < gb && wl < ntodo) {
             cl = RETRY ? (wl < nq ? A.queue[wl] : A.gqueue[wl - nq]) : (int32_t)wl;
-            const uint8_t st = A.cstat[cl];
-            if ((RETRY || !(st & VT_CELL_RETRIED)) && !(st & VT_CELL_FAILED)) {
-                const int32_t j0 = A.cells[cl];
-                vl = A.value[A.srow[j0]];
+            if (RETRY || !(A.cstat[cl] & VT_CELL_RETRIED)) {
+                jl = A.cells[cl];
+                vl = A.gval[jl];
                 if (vl != 0.0) {
-                    gpos<PT4>(A.spos, j0, xl, yl, zl);
-                    const double xq[3] = {xl, yl, zl};
-                    const double rc = A.crad[cl];
-                    int64_t va[3];
-                    bool one = true;
-                    for (int a = 0; a < 3; ++a) {
-                        const double g = xq[a] - it.lo[a];
-                        va[a] = (int64_t)floor((g - rc - del[a]) * ih[a]);
-                        one = one && va[a] == (int64_t)floor((g + rc - del[a]) * ih[a]);
-                    }
-                    if (one) {
-                        int64_t g = (wrapi(va[0], dims[0]) * dims[1] + wrapi(va[1], dims[1])) * dims[2] + wrapi(va[2], dims[2]);
-                        unsafeAtomicAdd(&A.grid[g], vl * A.cvol[cl] / hv);
-                    } else {
-                        todo = true;
-                    }
+                    lowl = A.glow[jl];
+                    gpos<PT4>(A.spos, jl, xl, yl, zl);
                 }
             }
         }
+        const bool todo = vl != 0.0;
         uint64_t tm = __ballot(todo);
         while (tm) {
             const int l = __builtin_ctzll(tm);
             tm &= tm - 1ull;
             const int32_t c = (int32_t)readlane_u32((uint32_t)cl, l);
-            const double val = readlane_d(vl, l);
+            const int32_t j0 = (int32_t)readlane_u32((uint32_t)jl, l), low = (int32_t)readlane_u32((uint32_t)lowl, l);
+            const double wi = readlane_d(vl, l);
             const double sx = readlane_d(xl, l), sy = readlane_d(yl, l), sz = readlane_d(zl, l);
             const double xs[3] = {sx, sy, sz};
-            const double vscale = val / hv;
             double blo[3], bhi[3];
             for (int a = 0; a < 3; ++a) {
                 if (it.periodic) {
@@ -388,36 +404,33 @@ __device__ __forceinline__ void grid_body(const GridArgs &A, char *smem, int wid
                 }
             }
             // seed position in the grid frame; grid line m of axis a lies at m h + del - g0 from the seed
-            const double g0[3] = {xs[0] - it.lo[0], xs[1] - it.lo[1], xs[2] - it.lo[2]};
-            int64_t i0[3], i1[3];
+            const double g0[3] = {uni_d(xs[0] - it.lo[0]), uni_d(xs[1] - it.lo[1]), uni_d(xs[2] - it.lo[2])};
+            int i0[3], i1[3];  // 32 bits: the faces' ranges in LDS and the queued items hold no more
             bool sane = true;
             for (int a = 0; a < 3; ++a) {
-                mn[a] = uni_d(wave_min(mn[a]));
-                mx[a] = uni_d(wave_max(mx[a]));
+                mn[a] = uni_d(wave_min_x(mn[a]));
+                mx[a] = uni_d(wave_max_x(mx[a]));
                 // a cell spans less than the box (2R < L/2 when periodic): its voxel range is at most
                 // the grid's; anything else (a vertex not finite, or far away) is a broken cell, and
                 // it must not drive the loops below
                 const double lo_ = (g0[a] + mn[a] - del[a]) * ih[a], hi_ = (g0[a] + mx[a] - del[a]) * ih[a];
                 sane = sane && isfinite(lo_) && isfinite(hi_) && hi_ >= lo_ && hi_ - lo_ <= (double)dims[a] + 1.0 &&
-                       fabs(lo_) < 1e15 && fabs(hi_) < 1e15;
-                i0[a] = sane ? (int64_t)floor(lo_) : 0;
-                i1[a] = sane ? (int64_t)floor(hi_) : 0;
+                       fabs(lo_) < 1e9 && fabs(hi_) < 1e9;
+                i0[a] = uni_i(sane ? (int)floor(lo_) : 0);
+                i1[a] = uni_i(sane ? (int)floor(hi_) : 0);
             }
             if (!sane) {
                 if (lane == 0) atomicOr(&A.counters[CTR_STATUS], VT_DEV_TOPOLOGY);
                 continue;
             }
-            if (i0[0] == i1[0] && i0[1] == i1[1] && i0[2] == i1[2]) {
-                if (lane == 0) {
-                    int64_t g = (wrapi(i0[0], dims[0]) * dims[1] + wrapi(i0[1], dims[1])) * dims[2] + wrapi(i0[2], dims[2]);
-                    unsafeAtomicAdd(&A.grid[g], val * A.cvol[c] / hv);
-                }
-                continue;
-            }
+            // full voxels below a face count down to the cell's lowest one, the same for every face of
+            // the cell whichever of its two cells integrates it
+            if (A.share) i0[0] = low;
             // the cell's voxel box: contributions are summed in LDS when it fits, and each voxel
             // then takes one global atomic
-            const int64_t bx = i1[0] - i0[0] + 1, by = i1[1] - i0[1] + 1, bz = i1[2] - i0[2] + 1;
-            const int nacc = bx * by * bz <= M::ACC ? (int)(bx * by * bz) : 0;
+            const int bx = i1[0] - i0[0] + 1, by = i1[1] - i0[1] + 1, bz = i1[2] - i0[2] + 1;
+            const int64_t nbox = (int64_t)bx * by * bz;
+            const int nacc = bx <= M::ACC && by <= M::ACC && bz <= M::ACC && nbox <= M::ACC ? (int)nbox : 0;
             for (int t = lane; t < nacc; t += 64) S.acc[t] = 0.0;
             // ---- faces: compact the alive ones
             int nf = 0;
@@ -427,6 +440,48 @@ __device__ __forceinline__ void grid_body(const GridArgs &A, char *smem, int wid
                 if (m & mybit) S.fid[nf + __popcll(m & lt)] = r * 64 + lane;
                 nf += __popcll(m);
             }
+            wave_sync();
+            // Of the faces shared with a cell that takes part, this cell integrates those where its
+            // lowest x voxel is the lower one (ties by index; the neighbour decides alike from its
+            // side), for both: the integrals are the same with opposite signs, so the voxels take them
+            // with the difference of the weights.  A full voxel below the face counts for each of the
+            // two down to that cell's lowest voxel, and the lower of the two lies in this cell's box.
+            {
+                int nown = 0;
+                for (int base = 0; base < nf; base += 64) {
+                    const int q = base + lane;
+                    bool own = q < nf;
+                    int f = 0, fl = INT32_MIN;
+                    double w = wi;
+                    if (own) {
+                        f = S.fid[q];
+                        const int32_t tag = S.P.ptag[f];
+                        const double wj = A.share && tag >= 0 ? A.gval[tag] : 0.0;
+                        if (wj != 0.0) {
+                            int lj = A.glow[tag];
+                            if (it.periodic) {
+                                double jx, jy, jz;
+                                gpos<PT4>(A.spos, tag, jx, jy, jz);
+                                lj -= (int)rint((jx - sx) * (1.0 / it.L[0])) * dims[0];
+                            }
+                            own = i0[0] < lj || (i0[0] == lj && j0 < tag);
+                            w = wi - wj;
+                            fl = lj;
+                        }
+                    }
+                    const uint64_t om = __ballot(own);
+                    wave_sync();
+                    if (own) {
+                        const int k = nown + __popcll(om & lt);
+                        S.fid[k] = f;
+                        S.fw[k] = w;
+                        S.flow[k] = fl;
+                    }
+                    nown += __popcll(om);
+                }
+                nf = nown;
+            }
+            if (nf == 0) continue;
             wave_sync();
             // the vertex after u on face f, counter-clockwise seen from outside
             auto next_on = [&](int f, const uint64_t *mf, int u) -> int {
@@ -456,14 +511,29 @@ __device__ __forceinline__ void grid_body(const GridArgs &A, char *smem, int wid
                 }
                 if constexpr (VPL == 1) {
                     // faces in order of loop length: the work items a wave takes at once then
-                    // mostly share a loop length, and fewer lanes idle in the loop over edges
-                    uint64_t kk[1] = {q < nf ? (((uint64_t)len << 8) | (uint64_t)lane) : ~0ull};
-                    bitonic_u64<1>(kk);
-                    const int src = (int)(kk[0] & 63ull);
+                    // mostly share a loop length, and fewer lanes idle in the loop over edges.  A
+                    // counting sort: one ballot per length, lane k learns which face comes k-th
+                    // through LDS.
+                    int rank = 0, done = 0;
+                    for (int m = 0; done < nf; ++m) {
+                        const uint64_t b = __ballot(q < nf && len == m);
+                        if (len == m) rank = done + __popcll(b & lt);
+                        done += __popcll(b);
+                    }
+                    if (q < nf) S.ipre[rank] = lane;
+                    wave_sync();
+                    const int src = q < nf ? S.ipre[lane] : lane;
                     const int len_s = __shfl(len, src), f_s = __shfl(f, src);
                     len = q < nf ? len_s : 0;
                     f = f_s;
-                    if (q < nf) S.fid[q] = f;
+                    const double w_s = S.fw[src];
+                    const int fl_s = S.flow[src];
+                    wave_sync();
+                    if (q < nf) {
+                        S.fid[q] = f;
+                        S.fw[q] = w_s;
+                        S.flow[q] = fl_s;
+                    }
                 }
                 if (q < nf) {
                     const P4<double> &pf = S.P.pl64[f];
@@ -488,7 +558,7 @@ __device__ __forceinline__ void grid_body(const GridArgs &A, char *smem, int wid
             }
             // loops, counter-clockwise in the (y, z) projection (faces seen from -x are reversed);
             // extents and work items: rectangles x (1 + planes strictly inside the face's x range)
-            int nitem = 0;
+            int nitem = 0, nlist = 0;
             bool big = false, open_loop = false;
             for (int base = 0; base < nf; base += 64) {
                 const int q = base + lane;
@@ -520,30 +590,37 @@ __device__ __forceinline__ void grid_body(const GridArgs &A, char *smem, int wid
                     const double nlen = sqrt(S.fn[q][0] * S.fn[q][0] + S.fn[q][1] * S.fn[q][1] + S.fn[q][2] * S.fn[q][2]);
                     // faces parallel to x add nothing (n_x = 0); nearly parallel ones are bounded by 1e-12 of a voxel
                     if (fabs(S.fn[q][0]) > 1e-12 * nlen) {
-                        const int64_t ja = (int64_t)floor((g0[1] + b[2] - del[1]) * ih[1]);
-                        const int64_t jb = (int64_t)floor((g0[1] + b[3] - del[1]) * ih[1]);
-                        const int64_t ka = (int64_t)floor((g0[2] + b[4] - del[2]) * ih[2]);
-                        const int64_t kb = (int64_t)floor((g0[2] + b[5] - del[2]) * ih[2]);
+                        int ja = (int)floor((g0[1] + b[2] - del[1]) * ih[1]);
+                        int jb = (int)floor((g0[1] + b[3] - del[1]) * ih[1]);
+                        int ka = (int)floor((g0[2] + b[4] - del[2]) * ih[2]);
+                        int kb = (int)floor((g0[2] + b[5] - del[2]) * ih[2]);
                         // planes X_m = m h + del with xmin < X_m < xmax (grid frame)
-                        const int64_t m0 = (int64_t)floor((g0[0] + b[0] - del[0]) * ih[0]) + 1;
-                        const int64_t m1 = (int64_t)ceil((g0[0] + b[1] - del[0]) * ih[0]);
-                        S.frect[q][0] = (int)ja;
-                        S.frect[q][1] = (int)(jb - ja + 1);
-                        S.frect[q][2] = (int)ka;
-                        S.frect[q][3] = (int)(kb - ka + 1);
-                        S.fpl[q][0] = (int)m0;
-                        S.fpl[q][1] = (int)(m1 > m0 ? m1 - m0 : 0);
+                        int m0 = (int)floor((g0[0] + b[0] - del[0]) * ih[0]) + 1;
+                        int m1 = (int)ceil((g0[0] + b[1] - del[0]) * ih[0]);
+                        S.frect[q][0] = ja;
+                        S.frect[q][1] = jb - ja + 1;
+                        S.frect[q][2] = ka;
+                        S.frect[q][3] = kb - ka + 1;
+                        S.fpl[q][0] = m0;
+                        S.fpl[q][1] = m1 > m0 ? m1 - m0 : 0;
                         // queued items hold the rectangle offsets in 20 bits and the plane index in 16
                         if (jb - ja + 1 >= (1 << 20) || kb - ka + 1 >= (1 << 20) || m1 - m0 + 1 >= (1 << 16)) big = true;
                         else items = S.frect[q][1] * S.frect[q][3] * (1 + S.fpl[q][1]);
                     }
                 }
+                // the faces with items, in order, and where their items start
                 int tot;
                 const int pre = wave_excl_scan(items, &tot);
-                if (q < nf) S.ipre[q] = nitem + pre;
+                const uint64_t im = __ballot(items > 0);
+                wave_sync();
+                if (items > 0) {
+                    const int k = nlist + __popcll(im & lt);
+                    S.fid[k] = q;
+                    S.ipre[k] = nitem + pre;
+                }
+                nlist += __popcll(im);
                 nitem += tot;
             }
-            if (lane == 0) S.ipre[nf] = nitem;
             wave_sync();
             nitem = uni_i(nitem);
             if (__ballot(big)) {
@@ -555,15 +632,15 @@ __device__ __forceinline__ void grid_body(const GridArgs &A, char *smem, int wid
                 continue;
             }
             // ---- work items
-            auto emit = [&](int64_t i, int64_t j, int64_t k, double v) {
+            auto emit = [&](int i, int j, int k, double v) {
                 if (v == 0.0) return;
-                const int64_t li = i - i0[0], lj = j - i0[1], lk = k - i0[2];
-                if (nacc > 0 && li >= 0 && li < bx && lj >= 0 && lj < by && lk >= 0 && lk < bz) {
+                const int li = i - i0[0], lj = j - i0[1], lk = k - i0[2];
+                if (nacc > 0 && (unsigned)li < (unsigned)bx && (unsigned)lj < (unsigned)by && (unsigned)lk < (unsigned)bz) {
                     unsafeAtomicAdd(&S.acc[(li * by + lj) * bz + lk], v);
                     return;
                 }
                 int64_t g = (wrap1(i, dims[0]) * dims[1] + wrap1(j, dims[1])) * dims[2] + wrap1(k, dims[2]);
-                unsafeAtomicAdd(&A.grid[g], v * vscale);
+                unsafeAtomicAdd(&A.grid[g], v);
             };
             // The item's geometry: rectangle corner (seed-relative; integrals are taken relative
             // to it), the face plane n.v = d, and the plane X.  With y, z relative to the corner the
@@ -573,7 +650,7 @@ __device__ __forceinline__ void grid_body(const GridArgs &A, char *smem, int wid
             // -G to voxel m-1 and +G to voxel m.
             struct ItemGeo {
                 double Y0, Z0, X, e, hs;
-                int64_t jj, kk, mm;
+                int jj, kk, mm;
             };
             auto geometry = [&](int q, int pi, int rj, int rk) -> ItemGeo {
                 ItemGeo G_;
@@ -581,7 +658,7 @@ __device__ __forceinline__ void grid_body(const GridArgs &A, char *smem, int wid
                 G_.kk = S.frect[q][2] + rk;
                 G_.Y0 = G_.jj * h[1] + del[1] - g0[1];
                 G_.Z0 = G_.kk * h[2] + del[2] - g0[2];
-                G_.mm = (int64_t)S.fpl[q][0] + pi - 1;
+                G_.mm = S.fpl[q][0] + pi - 1;
                 G_.X = G_.mm * h[0] + del[0] - g0[0];
                 G_.e = S.fn[q][3] - S.fn[q][0] * G_.X - S.fn[q][1] * G_.Y0 - S.fn[q][2] * G_.Z0;
                 G_.hs = S.fn[q][0] > 0.0 ? 1.0 : -1.0;
@@ -596,105 +673,144 @@ __device__ __forceinline__ void grid_body(const GridArgs &A, char *smem, int wid
             // from the lowest up to the first that cuts the face over R, as the bound above falls
             // with X).  The others are queued and integrated 64 at a time, so the lanes of an
             // integration pass all have an item.
-            // The two kinds of item go to rings of their own and are integrated 64 at a time, each
-            // kind by its own specialisation: a face's lowest plane (pi == 0) never clips the face
-            // with H, and a queued plane above it (pi > 0) always does, since it is queued only
-            // when the face lies on both sides of it over R (above_min < 0).
-            int head[2] = {0, 0}, qn[2] = {0, 0};
-            auto integrate = [&](auto kind, bool last) {
-                constexpr bool useH = decltype(kind)::value;
-                constexpr int w = useH ? 1 : 0;
-                while (qn[w] >= 64 || (last && qn[w] > 0)) {
-                    wave_sync();
-                    const int take = qn[w] < 64 ? qn[w] : 64;
-                    if (lane < take) {
-                        const uint64_t d = S.iq[w][(head[w] + lane) & 127];
-                        const int q = (int)(d & 0xFFull), pi = (int)((d >> 8) & 0xFFFFull);
-                        const int rj = (int)((d >> 24) & 0xFFFFFull), rk = (int)((d >> 44) & 0xFFFFFull);
-                        const ItemGeo g = geometry(q, pi, rj, rk);
-                        const double nx_ = S.fn[q][0], ny_ = S.fn[q][1], nz_ = S.fn[q][2];
-                        const double hs = g.hs, rnx = 1.0 / nx_;
-                        const int o = S.loff[q], m = S.loff[q + 1] - o;
-                        const Reg Rg = region_integrals<VPL, useH>(S, o, m, g.Y0, g.Z0, h[1], h[2], hs, g.e, ny_, nz_, g.X, rnx);
-                        const double G = hs * Rg.G;
-                        if constexpr (!useH) {
-                            if (Rg.A != 0.0) {
-                                // full voxels below the face's x minimum, within the cell's own range
-                                const int64_t iend = g.mm < i0[0] + bx ? g.mm : i0[0] + bx;
-                                for (int64_t i = i0[0]; i < iend; ++i) emit(i, g.jj, g.kk, hs * h[0] * Rg.A);
-                                emit(g.mm, g.jj, g.kk, G);
-                                // the planes with the face entirely above them over R (classified
-                                // with the same geometry and bound, so none is queued as well)
-                                const double cy_ = -hs * ny_ * h[1], cz_ = -hs * nz_ * h[2];
-                                const int npl = S.fpl[q][1];
+            // (Two rings, a lowest plane integrated by code without the chord, left two passes a cell
+            // mostly idle once a face is integrated for both its cells: 24.2 ms at 2M/256^3.)
+            int head = 0, qn = 0, rcur = 0;
+            auto integrate = [&](int take) {
+                wave_sync();
+                if (lane < take) {
+                    const uint64_t d = S.iq[(head + lane) & 127];
+                    const int q = (int)(d & 0xFFull), pi = (int)((d >> 8) & 0xFFFFull);
+                    const int rj = (int)((d >> 24) & 0xFFFFFull), rk = (int)((d >> 44) & 0xFFFFFull);
+                    const ItemGeo g = geometry(q, pi, rj, rk);
+                    const double nx_ = S.fn[q][0], ny_ = S.fn[q][1], nz_ = S.fn[q][2];
+                    const double hs = g.hs, rnx = 1.0 / nx_;
+                    const int o = S.loff[q], m = S.loff[q + 1] - o;
+                    // a face's lowest plane clips nothing of it: the chord is taken one plane further
+                    // down, clear of the face (X itself may round to either side of its x minimum)
+                    const double eH = pi == 0 ? fma(nx_, h[0], g.e) : g.e;
+                    const Reg Rg = region_integrals<VPL>(S, o, m, g.Y0, g.Z0, h[1], h[2], ih[1], ih[2], hs, eH, ny_, nz_, g.X, rnx);
+                    const double fw = S.fw[q];
+                    const double G = hs * Rg.G * fw;
+                    if (pi > 0) {
+                        emit(g.mm - 1, g.jj, g.kk, -G);
+                        emit(g.mm, g.jj, g.kk, G);
+                    } else if (Rg.A != 0.0) {
+                        // full voxels below the face's x minimum, within the cell's own range
+                        const int iend = min(g.mm, i1[0] + 1);
+                        const int fl = S.flow[q];
+                        const double full = hs * h[0] * Rg.A;
+                        for (int i = i0[0]; i < iend; ++i) emit(i, g.jj, g.kk, full * (i < fl ? wi : fw));
+                        emit(g.mm, g.jj, g.kk, G);
+                        // the planes with the face entirely above them over R (classified
+                        // with the same geometry and bound, so none is queued as well)
+                        const double cy_ = -hs * ny_ * h[1], cz_ = -hs * nz_ * h[2];
+                        const int npl = S.fpl[q][1];
 #pragma unroll 1
-                                for (int p = 1; p <= npl; ++p) {
-                                    // geometry(q, p, rj, rk)'s X and e, the same expressions
-                                    const int64_t mp = (int64_t)S.fpl[q][0] + p - 1;
-                                    const double Xp = mp * h[0] + del[0] - g0[0];
-                                    const double ep = S.fn[q][3] - S.fn[q][0] * Xp - S.fn[q][1] * g.Y0 - S.fn[q][2] * g.Z0;
-                                    if (hs * ep + fmin(0.0, cy_) + fmin(0.0, cz_) < 0.0) break;
-                                    const double Gp = hs * (Rg.G + (g.X - Xp) * Rg.A);
-                                    emit(mp - 1, g.jj, g.kk, -Gp);
-                                    emit(mp, g.jj, g.kk, Gp);
-                                }
-                            }
-                        } else {
-                            emit(g.mm - 1, g.jj, g.kk, -G);
-                            emit(g.mm, g.jj, g.kk, G);
+                        for (int p = 1; p <= npl; ++p) {
+                            // geometry(q, p, rj, rk)'s X and e, the same expressions
+                            const int mp = S.fpl[q][0] + p - 1;
+                            const double Xp = mp * h[0] + del[0] - g0[0];
+                            const double ep = S.fn[q][3] - S.fn[q][0] * Xp - S.fn[q][1] * g.Y0 - S.fn[q][2] * g.Z0;
+                            if (hs * ep + fmin(0.0, cy_) + fmin(0.0, cz_) < 0.0) break;
+                            const double Gp = hs * (Rg.G + (g.X - Xp) * Rg.A) * fw;
+                            emit(mp - 1, g.jj, g.kk, -Gp);
+                            emit(mp, g.jj, g.kk, Gp);
                         }
                     }
-                    head[w] += take;
-                    qn[w] -= take;
-                    wave_sync();
                 }
+                head += take;
+                qn -= take;
+                wave_sync();
             };
             for (int base = 0; base < nitem; base += 64) {
                 const int item = base + lane;
                 bool need = false;
-                int kind = 0;
                 uint64_t desc = 0;
+                // the starts of the next 64 listed faces, as bits of this chunk, give each lane its face
+                const int kn = rcur + 1 + lane;
+                const int st = kn < nlist ? S.ipre[kn] - base : 64;
+                const uint64_t starts = wave_or_u64(st < 64 ? 1ull << st : 0ull);
+                const int li = rcur + __popcll(starts & ((2ull << lane) - 1ull));
+                rcur = __builtin_amdgcn_readlane(li, 63);
                 if (item < nitem) {
-                    int lo = 0, hi = nf - 1;
-                    while (lo < hi) {
-                        int mid = (lo + hi + 1) >> 1;
-                        if (S.ipre[mid] <= item) lo = mid; else hi = mid - 1;
-                    }
-                    const int q = lo;
+                    const int q = S.fid[li];
                     int pi, rj;
-                    const int r = divmod_small(item - S.ipre[q], 1 + S.fpl[q][1], pi);
+                    const int r = divmod_small(item - S.ipre[li], 1 + S.fpl[q][1], pi);
                     const int rk = divmod_small(r, S.frect[q][1], rj);
                     const ItemGeo g = geometry(q, pi, rj, rk);
                     const double cy_ = -g.hs * S.fn[q][1] * h[1], cz_ = -g.hs * S.fn[q][2] * h[2];
                     const double above_max = g.hs * g.e + fmax(0.0, cy_) + fmax(0.0, cz_);
                     const double above_min = g.hs * g.e + fmin(0.0, cy_) + fmin(0.0, cz_);
                     need = pi == 0 || (above_max > 0.0 && above_min < 0.0);
-                    kind = pi == 0 ? 0 : 1;
                     desc = (uint64_t)q | ((uint64_t)pi << 8) | ((uint64_t)rj << 24) | ((uint64_t)rk << 44);
                 }
-                const uint64_t n0 = __ballot(need && kind == 0), n1 = __ballot(need && kind == 1);
-                if (need) {
-                    const uint64_t nb = kind == 0 ? n0 : n1;
-                    S.iq[kind][(head[kind] + qn[kind] + __popcll(nb & lt)) & 127] = desc;
-                }
-                qn[0] += __popcll(n0);
-                qn[1] += __popcll(n1);
+                const uint64_t nm = __ballot(need);
+                if (need) S.iq[(head + qn + __popcll(nm & lt)) & 127] = desc;
+                qn += __popcll(nm);
                 const bool last = base + 64 >= nitem;
-                integrate(std::integral_constant<bool, false>(), last);
-                integrate(std::integral_constant<bool, true>(), last);
+                while (qn >= 64 || (last && qn > 0)) integrate(min(qn, 64));
             }
             wave_sync();
             for (int t = lane; t < nacc; t += 64) {
                 const double v = S.acc[t];
                 if (v != 0.0) {
-                    const int64_t lk = t % bz, lj = (t / bz) % by, li = t / (by * bz);
+                    int lk, lj;
+                    const int li = divmod_small(divmod_small(t, bz, lk), by, lj);
                     const int64_t g = (wrap1(i0[0] + li, dims[0]) * dims[1] + wrap1(i0[1] + lj, dims[1])) * dims[2] +
                                       wrap1(i0[2] + lk, dims[2]);
-                    unsafeAtomicAdd(&A.grid[g], v * vscale);
+                    unsafeAtomicAdd(&A.grid[g], v);
                 }
             }
         }
     }
+}
+
+// Before the deposit: each sorted particle's weight (0 for buffer particles, failed cells and zero
+// values) and its cell's lowest x voxel, which the faces of its neighbours read.  A cell inside one
+// voxel (its ball of radius R, the largest vertex distance, is) deposits its whole volume here and
+// takes no further part.
+template <typename PT4>
+__global__ void __launch_bounds__(256) k_grid_weights(GridArgs A, const int32_t *srow, const int32_t *row2cell,
+                                                      const double *value, double *gval, int32_t *glow) {
+    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    // the deposit's counters start at zero
+    if (blockIdx.x == 0 && threadIdx.x < VT_XCD_SEGMENTS) A.counters[CTR_SEG(threadIdx.x)] = 0;
+    if (j == 0) A.counters[CTR_GRID] = A.counters[CTR_GRID_RETRY] = A.counters[CTR_DEBUG] = A.counters[CTR_GRID_Q] = 0;
+    if (j >= A.npos) return;
+    double w = 0.0;
+    int32_t low = 0;
+    const int32_t row = srow[j];
+    if (row >= 0) {
+        const double v = value[row];
+        const int32_t c = row2cell[row];
+        if (v != 0.0 && !(A.cstat[c] & VT_CELL_FAILED)) {
+            const DevItem it = A.items[0];
+            const int dims[3] = {A.nx, A.ny, A.nz};
+            double x[3], hv = 1.0;
+            gpos<PT4>(A.spos, (int32_t)j, x[0], x[1], x[2]);
+            const double rc = A.crad[c];
+            int64_t va[3];
+            bool one = true;
+            for (int a = 0; a < 3; ++a) {
+                const double h = it.L[a] / dims[a], ih = 1.0 / h, del = 1e-12 * h;
+                const double g = x[a] - it.lo[a];
+                hv *= h;
+                va[a] = (int64_t)floor((g - rc - del) * ih);
+                one = one && va[a] == (int64_t)floor((g + rc - del) * ih);
+                // widened: no vertex may round to a voxel below
+                if (a == 0) low = (int32_t)floor((g - rc * (1.0 + 1e-9) - 2.0 * del) * ih);
+            }
+            if (one) {
+                const int64_t g = (wrapi(va[0], dims[0]) * dims[1] + wrapi(va[1], dims[1])) * dims[2] + wrapi(va[2], dims[2]);
+                unsafeAtomicAdd(&A.grid[g], v * A.cvol[c] / hv);
+            } else {
+                w = v / hv;
+            }
+        }
+    }
+    gval[j] = w;
+    glow[j] = low;
 }
 
 template <typename PT4, int VPL, bool RETRY>
@@ -1319,9 +1435,10 @@ static hipError_t launch_grid_fused(vt_ctx *c, GridArgs &a) {
 // The normal kernel with the large one over the clip's retry queue in one launch, then the large
 // kernel over the cells the normal one handed over.
 template <typename PT4>
-static hipError_t launch_grid_all(vt_ctx *c, GridArgs &a) {
-    hipError_t e = launch_grid_fused<PT4>(c, a);
-    if (e == hipSuccess) e = vt_launch_zero_u32(c->counters + CTR_GRID, 1, c->stream);
+static hipError_t launch_grid_all(vt_ctx *c, GridArgs &a, const double *value, double *gval, int32_t *glow) {
+    k_grid_weights<PT4><<<(unsigned)((a.npos + 255) / 256), 256, 0, c->stream>>>(a, c->srow, c->row2cell, value, gval, glow);
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess) e = launch_grid_fused<PT4>(c, a);
     if (e != hipSuccess) return e;
     a.seg = 2;
     a.n_large = 0;
@@ -1331,8 +1448,6 @@ static hipError_t launch_grid_all(vt_ctx *c, GridArgs &a) {
 hipError_t vt_launch_grid(vt_ctx *c, const double *value, int nx, int ny, int nz, double *grid) {
     const int64_t ng = (int64_t)nx * ny * nz;
     k_zero_f64<<<(ng + 255) / 256, 256, 0, c->stream>>>(grid, ng);
-    hipError_t ez = vt_launch_zero_u32(c->counters + CTR_GRID, CTR_GRID_Q - CTR_GRID + 1, c->stream);
-    if (ez != hipSuccess) return ez;
     GridArgs a;
     a.spos = c->spos;
     a.items = c->items;
@@ -1352,8 +1467,15 @@ hipError_t vt_launch_grid(vt_ctx *c, const double *value, int nx, int ny, int nz
     a.cnv = c->cnv;
     a.npos = c->n_total;
     a.stage_ids = c->stage_ids;
-    a.srow = c->srow;
-    a.value = value;
+    // the weights lie in the sort's spare key and value buffers, free after the build
+    double *gval = (double *)(c->skey == c->keys[0] ? c->keys[1] : c->keys[0]);
+    int32_t *glow = (int32_t *)c->vals[0];
+    a.gval = gval;
+    a.glow = glow;
+    // voxel indices of the x axis are kept in 32 bits, with room for a period to either side
+    a.share = nx <= (1 << 29) ? 1 : 0;
+    // as many cells at a time as leave every resident wavefront (two per SIMD) a few turns
+    a.batch = (int)std::max<int64_t>(1, std::min<int64_t>(GRID_BATCH, c->n_owned / (4 * 2048)));
     a.counters = c->counters;
     a.grid = grid;
     a.nx = nx;
@@ -1361,5 +1483,6 @@ hipError_t vt_launch_grid(vt_ctx *c, const double *value, int nx, int ny, int nz
     a.nz = nz;
     a.seg = 0;
     a.n_large = 0;
-    return c->dtype == VT_F32 ? launch_grid_all<float4>(c, a) : launch_grid_all<double4>(c, a);
+    return c->dtype == VT_F32 ? launch_grid_all<float4>(c, a, value, gval, glow)
+                              : launch_grid_all<double4>(c, a, value, gval, glow);
 }
