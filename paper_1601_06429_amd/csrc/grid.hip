@@ -418,6 +418,11 @@ __device__ __forceinline__ void grid_body(const GridArgs &A, char *smem, int wid
                        fabs(lo_) < 1e9 && fabs(hi_) < 1e9;
                 i0[a] = uni_i(sane ? (int)floor(lo_) : 0);
                 i1[a] = uni_i(sane ? (int)floor(hi_) : 0);
+                if (!it.periodic) {
+                    // a wall of a bounded box is its first or last grid line, not a plane to cut at
+                    i0[a] = max(i0[a], 0);
+                    i1[a] = min(i1[a], dims[a] - 1);
+                }
             }
             if (!sane) {
                 if (lane == 0) atomicOr(&A.counters[CTR_STATUS], VT_DEV_TOPOLOGY);
@@ -597,6 +602,17 @@ __device__ __forceinline__ void grid_body(const GridArgs &A, char *smem, int wid
                         // planes X_m = m h + del with xmin < X_m < xmax (grid frame)
                         int m0 = (int)floor((g0[0] + b[0] - del[0]) * ih[0]) + 1;
                         int m1 = (int)ceil((g0[0] + b[1] - del[0]) * ih[0]);
+                        if (!it.periodic) {
+                            // A face that ends on a wall crosses that wall's grid line (moved by del)
+                            // next to its own edge there; cut at it, a face steep in x has a chord
+                            // that rounding cannot tell from the edge.
+                            ja = min(max(ja, 0), dims[1] - 1);
+                            jb = min(max(jb, 0), dims[1] - 1);
+                            ka = min(max(ka, 0), dims[2] - 1);
+                            kb = min(max(kb, 0), dims[2] - 1);
+                            m0 = min(max(m0, 1), dims[0]);
+                            m1 = min(m1, dims[0]);
+                        }
                         S.frect[q][0] = ja;
                         S.frect[q][1] = jb - ja + 1;
                         S.frect[q][2] = ka;
@@ -800,6 +816,7 @@ __global__ void __launch_bounds__(256) k_grid_weights(GridArgs A, const int32_t 
                 one = one && va[a] == (int64_t)floor((g + rc - del) * ih);
                 // widened: no vertex may round to a voxel below
                 if (a == 0) low = (int32_t)floor((g - rc * (1.0 + 1e-9) - 2.0 * del) * ih);
+                if (a == 0 && !it.periodic) low = max(low, 0);
             }
             if (one) {
                 const int64_t g = (wrapi(va[0], dims[0]) * dims[1] + wrapi(va[1], dims[1])) * dims[2] + wrapi(va[2], dims[2]);

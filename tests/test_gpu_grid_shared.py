@@ -25,9 +25,8 @@ def _check(vt, torch_cuda, oracle, p, periodic, val, dims, items=None, ids=None)
     assert np.max(np.abs(g - ref)) <= tol
 
 
-@pytest.mark.parametrize("dims,periodic", [((1, 1, 1), True), ((3, 5, 2), True), ((11, 1, 40), True),
-                                           ((40, 33, 27), True), ((1, 1, 1), False), ((3, 5, 2), False),
-                                           ((40, 33, 27), False)])
+@pytest.mark.parametrize("dims", [(1, 1, 1), (3, 5, 2), (11, 1, 40), (40, 33, 27)])
+@pytest.mark.parametrize("periodic", [True, False])
 @pytest.mark.parametrize("dtype", [np.float32, np.float64])
 def test_mixed_values(vt, torch_cuda, oracle, dims, periodic, dtype):
     rng = np.random.default_rng(71)
