@@ -253,8 +253,9 @@ vt_status vt_grid_tensor(vt_ctx *ctx, const double *grid, int32_t nx, int32_t ny
  * device memory (code under HIP graph capture, tight serving loops, harnesses
  * that forbid hipMalloc): the same result, bit for bit, with the FFT scratch
  * taken from a static device array of the library instead of the context.  The
- * array serves grids of up to VT_NOALLOC_TENSOR_POINTS points; each device the library runs this on keeps its own copy (64 MiB) until the process
- * ends.  The call allocates nothing (no hipMalloc, hipFree or allocating
+ * array serves grids of up to VT_NOALLOC_TENSOR_POINTS points; each device the
+ * library runs this on keeps its own copy (64 MiB) until the process ends.  The
+ * call allocates nothing (no hipMalloc, hipFree or allocating
  * library routine).  Every call on one device shares that device's array, so
  * calls that overlap on one device (different streams, or different host
  * threads) race and must be serialised by the caller; the array needs no

@@ -124,6 +124,18 @@ __device__ __forceinline__ ClipArgsPtr clip_args() {
     return (ClipArgsPtr)p;
 }
 
+// The next four set bits of m (the last one repeated when fewer are left), cleared from it: the large
+// kernel, one wavefront per SIMD, tests four vertices per step with their LDS loads in flight together.
+__device__ __forceinline__ void take4(uint64_t &m, int k[4]) {
+    k[0] = __builtin_ctzll(m);
+    m &= m - 1;
+#pragma unroll
+    for (int i = 1; i < 4; ++i) {
+        k[i] = m ? __builtin_ctzll(m) : k[i - 1];
+        m &= m - 1;
+    }
+}
+
 __device__ __forceinline__ int find_item_d(const DevItem *items, int n_items, int64_t p) {
     int lo = 0, hi = n_items - 1;
     while (lo < hi) {
@@ -589,14 +601,22 @@ __device__ __forceinline__ void clip_cells(const ClipArgs &A) {
                     for (int s_ = 0; s_ < VPL; ++s_) {
                         uint64_t m = farv[s_];
                         while (m && !reached) {
-                            const int kv = __builtin_ctzll(m);
-                            m &= m - 1;
-                            const double *v = S.u.s.vp[s_ * 64 + kv];
-                            const double ex = fmax(0.0, fmax(bl[0] - v[0], v[0] - bh[0]));
-                            const double ey = fmax(0.0, fmax(bl[1] - v[1], v[1] - bh[1]));
-                            const double ez = fmax(0.0, fmax(bl[2] - v[2], v[2] - bh[2]));
-                            const double rv = S.u.s.vr[s_ * 64 + kv];
-                            reached = ex * ex + ey * ey + ez * ez < rv * rv;
+                            int kv[4];
+                            take4(m, kv);
+                            double v[4][4];
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) {
+                                const int k = s_ * 64 + kv[i];
+                                for (int a = 0; a < 3; ++a) v[i][a] = S.u.s.vp[k][a];
+                                v[i][3] = S.u.s.vr[k];
+                            }
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) {
+                                const double ex = fmax(0.0, fmax(bl[0] - v[i][0], v[i][0] - bh[0]));
+                                const double ey = fmax(0.0, fmax(bl[1] - v[i][1], v[i][1] - bh[1]));
+                                const double ez = fmax(0.0, fmax(bl[2] - v[i][2], v[i][2] - bh[2]));
+                                reached = reached || ex * ex + ey * ey + ez * ez < v[i][3] * v[i][3];
+                            }
                         }
                     }
                     return reached;
@@ -853,9 +873,17 @@ __device__ __forceinline__ void clip_cells(const ClipArgs &A) {
                 for (int s = 0; s < VPL; ++s) {
                     uint64_t m = vm[s];
                     while (m) {
-                        const int k = __builtin_ctzll(m);
-                        m &= m - 1;
-                        act |= cuts_v(s * 64 + k);
+                        if constexpr (RETRY) {
+                            int k[4];
+                            take4(m, k);
+                            const bool a0 = cuts_v(s * 64 + k[0]), a1 = cuts_v(s * 64 + k[1]),
+                                       a2 = cuts_v(s * 64 + k[2]), a3 = cuts_v(s * 64 + k[3]);
+                            act = act || a0 || a1 || a2 || a3;
+                        } else {
+                            const int k = __builtin_ctzll(m);
+                            m &= m - 1;
+                            act |= cuts_v(s * 64 + k);
+                        }
                     }
                 }
                 uint64_t am = __ballot(keep && act);
@@ -893,17 +921,20 @@ __device__ __forceinline__ void clip_cells(const ClipArgs &A) {
         for (int pass = 0; pass < 160; ++pass) {
             const double rh2 = uni_d(r_next * r_next), rl2 = uni_d(r_done * r_done);
             const double inv_rh2 = uni_d(1.0 / rh2), inv_bin = uni_d(64.0 / (rh2 - rl2));
-            int total;
+            int total = 0;
+            // The large kernel's later shells hold more particles than fit in LDS (its cells lie next to
+            // halos), and gathering them only to count them cost it most of its time: it sweeps at once.
+            const bool direct = RETRY && r_done > 0.0 && ncut >= 4;
             // once the cell has been cut a few times, covering boxes that no vertex's empty sphere
             // reaches hold no particle that can still cut it, as in the sweeps
             const bool prune = r_done > 0.0 && ncut >= 4;
-            if (prune) stage_search();
-            const int ncq = cover(r_next, r_done, total, prune);
+            if (prune && !direct) stage_search();
+            const int ncq = direct ? 0 : cover(r_next, r_done, total, prune);
             S.hist[lane] = 0;
             wave_sync();
             // ---- gather particles with r_done <= d < r_next (and a d^2 histogram); the positions
             // of the next 64 are loaded while the current 64 are processed
-            int n = 0;
+            int n = direct ? VT_CAND_MAX + 1 : 0;
             int32_t jn = -1;
             PT4 pn{};
             int rcur = 0;

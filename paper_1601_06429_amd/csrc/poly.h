@@ -550,6 +550,11 @@ struct Poly {
         bool any = false, all = true;
 #pragma unroll
         for (int s = 0; s < VPL; ++s) {
+            if (VPL > 1 && alive[s] == 0ull) {  // slots fill from the first word on
+                out[s] = false;
+                Mk[s] = 0ull;
+                continue;
+            }
             bool al = in_mask(alive[s]);
             T sv = side<T>(vx[s], vy[s], vz[s], p);
             bool o = sv > T(0);
@@ -585,6 +590,7 @@ struct Poly {
         for (int s = 0; s < VPL; ++s) {
             nbv[s] = 0;
             emask[s] = 0;
+            if (VPL > 1 && Mk[s] == 0ull) continue;
             if (out[s]) {
                 const uint32_t t = vt[s];
                 const int f0 = t & 0xFF, f1 = (t >> 8) & 0xFF, f2 = (t >> 16) & 0xFF;
@@ -673,6 +679,11 @@ struct Poly {
 #pragma unroll
         for (int s = 0; s < VPL; ++s) {
             const uint64_t F = ~alive[s] | Mk[s];
+            if (VPL > 1 && rank0 >= NB) {
+                alive[s] &= ~Mk[s];
+                if (lane == 0) S.fm[q][s] = 0ull;
+                continue;
+            }
             const int r = rank0 + rank_in(F);
             const bool got = in_mask(F) && r < NB;
             if (got) {
