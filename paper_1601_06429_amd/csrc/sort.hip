@@ -39,9 +39,17 @@ __device__ T block_exclusive_scan(T v, T *lds, T *total) {
     return incl - v;
 }
 
+// Up to three arrays of one length, back to back in `in`, are scanned side by side (blockIdx.y).
+template <typename T>
+struct ScanOut {
+    T *out[3];
+};
+
 template <typename T>
 __global__ void __launch_bounds__(SCAN_THREADS) k_scan_reduce(const T *in, int64_t n, int64_t *sums) {
     __shared__ int64_t lds[SCAN_THREADS];
+    in += blockIdx.y * n;
+    sums += blockIdx.y * (int64_t)(gridDim.x + 1);
     int64_t base = (int64_t)blockIdx.x * SCAN_TILE;
     int64_t acc = 0;
     for (int i = 0; i < SCAN_ITEMS; ++i) {
@@ -53,10 +61,11 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_scan_reduce(const T *in, int64
     if (threadIdx.x == 0) sums[blockIdx.x] = tot;
 }
 
-// single block: exclusive scan of the block sums (nb <= SCAN_THREADS * 64)
+// one block per array: exclusive scan of the block sums (nb <= SCAN_THREADS * 64)
 __global__ void __launch_bounds__(SCAN_THREADS) k_scan_top(int64_t *sums, int64_t nb) {
     __shared__ int64_t lds[SCAN_THREADS];
-    const int per = 64;
+    sums += blockIdx.x * (nb + 1);
+    const int per = (int)((nb + SCAN_THREADS - 1) / SCAN_THREADS);
     int64_t base = (int64_t)threadIdx.x * per;
     int64_t acc = 0;
     for (int i = 0; i < per; ++i)
@@ -73,9 +82,12 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_scan_top(int64_t *sums, int64_
 }
 
 template <typename T>
-__global__ void __launch_bounds__(SCAN_THREADS) k_scan_down(const T *in, T *out, int64_t n, const int64_t *sums,
+__global__ void __launch_bounds__(SCAN_THREADS) k_scan_down(const T *in, ScanOut<T> O, int64_t n, const int64_t *sums,
                                                             int write_total, int64_t nb) {
     __shared__ int64_t lds[SCAN_THREADS];
+    in += blockIdx.y * n;
+    sums += blockIdx.y * (nb + 1);
+    T *out = blockIdx.y == 0 ? O.out[0] : blockIdx.y == 1 ? O.out[1] : O.out[2];
     __shared__ T tile[SCAN_TILE];
     int64_t base = (int64_t)blockIdx.x * SCAN_TILE;
     for (int i = 0; i < SCAN_ITEMS; ++i) {
@@ -106,8 +118,10 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_scan_down(const T *in, T *out,
 
 // a scan of at most one tile: the block's own prefix, and the total, in one launch
 template <typename T>
-__global__ void __launch_bounds__(SCAN_THREADS) k_scan_single(const T *in, T *out, int64_t n) {
+__global__ void __launch_bounds__(SCAN_THREADS) k_scan_single(const T *in, ScanOut<T> O, int64_t n) {
     __shared__ int64_t lds[SCAN_THREADS];
+    in += blockIdx.x * n;
+    T *out = blockIdx.x == 0 ? O.out[0] : blockIdx.x == 1 ? O.out[1] : O.out[2];
     const int t = threadIdx.x;
     int64_t acc = 0;
     T loc[SCAN_ITEMS];
@@ -127,26 +141,32 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_scan_single(const T *in, T *ou
 }
 
 template <typename T>
-static hipError_t scan_impl(const T *in, T *out, int64_t n, int64_t *tmp, hipStream_t s) {
+static hipError_t scan_impl(const T *in, ScanOut<T> out, int count, int64_t n, int64_t *tmp, hipStream_t s) {
     int64_t nb = (n + SCAN_TILE - 1) / SCAN_TILE;
     if (nb == 0) nb = 1;
     if (nb > SCAN_THREADS * 64) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)nb, (unsigned)count);
     if (nb == 1) {
-        k_scan_single<T><<<1, SCAN_THREADS, 0, s>>>(in, out, n);
+        k_scan_single<T><<<count, SCAN_THREADS, 0, s>>>(in, out, n);
         return hipGetLastError();
     }
-    k_scan_reduce<T><<<nb, SCAN_THREADS, 0, s>>>(in, n, tmp);
-    k_scan_top<<<1, SCAN_THREADS, 0, s>>>(tmp, nb);
-    k_scan_down<T><<<nb, SCAN_THREADS, 0, s>>>(in, out, n, tmp, 1, nb);
+    k_scan_reduce<T><<<grid, SCAN_THREADS, 0, s>>>(in, n, tmp);
+    k_scan_top<<<count, SCAN_THREADS, 0, s>>>(tmp, nb);
+    k_scan_down<T><<<grid, SCAN_THREADS, 0, s>>>(in, out, n, tmp, 1, nb);
     return hipGetLastError();
 }
 
 // exclusive scan: out[0..n] with out[n] = total; in and out must not overlap
 hipError_t vt_launch_scan_i64(const int64_t *in, int64_t *out, int64_t n, int64_t *tmp, hipStream_t s) {
-    return scan_impl<int64_t>(in, out, n, tmp, s);
+    return scan_impl<int64_t>(in, ScanOut<int64_t>{{out, out, out}}, 1, n, tmp, s);
 }
 hipError_t vt_launch_scan_i32(const int32_t *in, int32_t *out, int64_t n, int64_t *tmp, hipStream_t s) {
-    return scan_impl<int32_t>(in, out, n, tmp, s);
+    return scan_impl<int32_t>(in, ScanOut<int32_t>{{out, out, out}}, 1, n, tmp, s);
+}
+// three arrays of n, back to back in `in`; tmp holds 3 vt_scan_tmp_elems(n)
+hipError_t vt_launch_scan3_i64(const int64_t *in, int64_t *o0, int64_t *o1, int64_t *o2, int64_t n, int64_t *tmp,
+                               hipStream_t s) {
+    return scan_impl<int64_t>(in, ScanOut<int64_t>{{o0, o1, o2}}, 3, n, tmp, s);
 }
 
 __global__ void k_zero_u32(uint32_t *p, int64_t n) {

@@ -10,12 +10,22 @@
 //   loops     loop_off[f] .. loop_off[f + 1], vertex indices local to the cell, counter-clockwise
 //             seen from outside, starting at the face's smallest index.
 // Two passes over the cells: the first counts (vertices, faces, loop entries) per row, the host
-// scans the counts, and the second writes, after checking that it finds the counted sizes.  A
-// cell of a periodic box with a topology record whose faces are all facets is counted from the
-// record alone (its vertices, its faces, three loop entries per vertex).  Each pass is one wavefront per cell: the cell is
-// rebuilt from its topology record (or its facets), its face loops are walked lane-parallel, one
-// face per lane, and sorted by neighbour id with a wave bitonic sort.  Cells with more than 64
-// vertices go to a large kernel with four vertex slots per lane.
+// scans the counts, and the second writes.
+//
+// Nearly every cell has a topology record whose faces are all in its facet list.  Such a cell is
+// counted by one thread (its vertices, its faces, three loop entries per vertex), and written by
+// k_structure_fast from the record alone: no face is dropped, the record's vertex triples are
+// counter-clockwise seen from outside, so a loop needs no area to know its direction, and the faces'
+// order is the rank of their ids.  A cell of the large clip kernel with F = V / 2 + 2 facets (a simple
+// polytope has that many faces) is counted alike.  The others (faces dropped, walls, no record) are
+// counted and written by k_structure: rebuilt, their face loops walked lane-parallel for area and
+// direction, one face per lane, and sorted by id with a wave bitonic sort; cells with more than 64
+// vertices by its large variant with four vertex slots per lane.
+//
+// Bound by the latency of dependent loads (cell -> seed -> row -> offsets, tags -> positions) and of
+// LDS.  400k clustered cells: the write pass 2.39 -> 0.42 ms (1.1 TB/s written; 79 vector registers
+// and 4.6 KB of LDS a wavefront, six per SIMD, the scalars of 16 cells loaded by the lanes together),
+// the count pass 0.48 -> 0.04 ms, the call with its sizing call 4.12 -> 0.98 ms.
 #include "rebuild.h"
 
 template <int VPL>
@@ -43,7 +53,8 @@ struct StructArgs {
     int64_t queue_cap;
     int32_t *squeue;          // cells the normal kernel could not hold, for the large kernel
     int64_t squeue_cap;
-    uint8_t *smark;           // per cell slot: 1 if the large kernel takes it
+    int32_t *slow;            // cells for the normal kernel
+    uint8_t *smark;           // per cell slot: who writes it (MARK_*)
     uint32_t *counters;
     float area_eps;
     int write;                // 0: count, 1: write
@@ -54,6 +65,10 @@ struct StructArgs {
     int64_t *loop_off;
     int32_t *loop_vert;
 };
+
+// which kernel writes a cell: from its record, the normal kernel, the large kernel (counted already
+// or by that kernel), or none (a failed cell)
+enum { MARK_FAST = 0, MARK_SLOW = 1, MARK_LARGE = 2, MARK_LARGE_COUNTED = 3, MARK_NONE = 4 };
 
 __device__ __forceinline__ int item_of(const DevItem *items, int n_items, int64_t p) {
     int lo = 0, hi = n_items - 1;
@@ -90,37 +105,17 @@ __global__ void __launch_bounds__(256) k_structure(StructArgs A) {
     const int lane = lane_id();
     const uint64_t lt = lanemask_lt();
     const int64_t nq = RETRY ? (int64_t)min((uint64_t)A.counters[CTR_QUEUE], (uint64_t)A.queue_cap) : 0;
-    const int64_t ntodo =
-        RETRY ? nq + (int64_t)min((uint64_t)A.counters[CTR_STRUCT_Q], (uint64_t)A.squeue_cap) : A.ncells;
+    const int64_t ntodo = RETRY ? nq + (int64_t)min((uint64_t)A.counters[CTR_STRUCT_Q], (uint64_t)A.squeue_cap)
+                                : (int64_t)A.counters[CTR_STRUCT_SLOW];
     const int64_t nwaves = (int64_t)gridDim.x * (blockDim.x >> 6);
     for (int64_t w = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); w < ntodo; w += nwaves) {
-        const int32_t c = RETRY ? (w < nq ? A.queue[w] : A.squeue[w - nq]) : (int32_t)w;
-        const uint8_t st = A.cstat[c];
+        const int32_t c = RETRY ? (w < nq ? A.queue[w] : A.squeue[w - nq]) : A.slow[w];
+        const uint8_t mark = A.smark[c];
+        // the write pass skips cells that the count pass handed to the large kernel
+        if (mark == MARK_NONE || (!RETRY && mark != MARK_SLOW) || (RETRY && !A.write && mark == MARK_LARGE_COUNTED)) continue;
         const int32_t j0 = A.cells[c];
         const int64_t row = A.srow[j0];
-        if (!RETRY) {
-            // cells the clip kernel retried belong to the large kernel, as do (in the write pass)
-            // the ones this kernel handed over in the count pass
-            if (st & VT_CELL_RETRIED) continue;
-            if (A.write && A.smark[c]) continue;
-            if (!A.write && lane == 0) A.smark[c] = 0;
-        }
-        if (st & VT_CELL_FAILED) {
-            if (!A.write && lane == 0) A.nvert[row] = A.nface[row] = A.nloop[row] = 0;
-            continue;
-        }
         const DevItem it = uniform_item(A.items[item_of(A.items, A.n_items, j0)]);
-        if (!RETRY && !A.write && it.periodic) {
-            const int nf = A.src.cnf[c], nv = A.src.cnv[c];
-            if (nf >= 4 && nf <= VT_TOPO_FACES && nv >= 4 && nv <= 64 && A.src.ccnt[c] == nf) {
-                if (lane == 0) {
-                    A.nvert[row] = nv;
-                    A.nface[row] = nf;
-                    A.nloop[row] = 3 * nv;
-                }
-                continue;
-            }
-        }
         double xs[3];
         gpos<PT4>(A.src.spos, j0, xs[0], xs[1], xs[2]);
         double blo[3], bhi[3];
@@ -138,7 +133,7 @@ __global__ void __launch_bounds__(256) k_structure(StructArgs A) {
         if (rb == REBUILD_OVERFLOW) {
             if (lane == 0) {
                 if (!A.write) {
-                    A.smark[c] = 1;
+                    A.smark[c] = MARK_LARGE;
                     const uint32_t qi = atomicAdd(&A.counters[CTR_STRUCT_Q], 1u);
                     if ((int64_t)qi < A.squeue_cap) A.squeue[qi] = c;
                     else atomicOr(&A.counters[CTR_STATUS], VT_DEV_CAPACITY);
@@ -305,6 +300,200 @@ __global__ void __launch_bounds__(256) k_structure(StructArgs A) {
     }
 }
 
+// The count pass, one thread per cell: the counts that follow without rebuilding the cell, and who
+// writes it.
+__global__ void __launch_bounds__(256) k_structure_count(StructArgs A) {
+    const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    bool slow = false;
+    if (c < A.ncells) {
+        const uint8_t st = A.cstat[c];
+        const int64_t row = A.srow[A.cells[c]];
+        const int nf = A.src.cnf[c], nv = A.src.cnv[c], fc = A.src.ccnt[c];
+        int64_t v = 0, f = 0;
+        uint8_t mark = MARK_SLOW;
+        if (st & VT_CELL_FAILED) {
+            mark = MARK_NONE;
+        } else if (st & VT_CELL_RETRIED) {
+            mark = nv >= 4 && 2 * fc == nv + 4 ? MARK_LARGE_COUNTED : MARK_LARGE;
+        } else if (nf >= 4 && nf <= VT_TOPO_FACES && nv >= 4 && nv <= 64 && fc == nf) {
+            mark = MARK_FAST;
+        }
+        if (mark == MARK_FAST || mark == MARK_LARGE_COUNTED) {
+            v = nv;
+            f = fc;
+        }
+        A.smark[c] = mark;
+        A.nvert[row] = v;
+        A.nface[row] = f;
+        A.nloop[row] = 3 * v;
+        slow = mark == MARK_SLOW;
+    }
+    const uint64_t m = __ballot(slow);
+    if (m != 0ull) {
+        uint32_t base = 0;
+        if (lane_id() == 0) base = atomicAdd(&A.counters[CTR_STRUCT_SLOW], (uint32_t)__popcll(m));
+        base = readlane_u32(base, 0);
+        if (slow) A.slow[base + rank_in(m)] = (int32_t)c;
+    }
+}
+
+// The write pass for cells written from their records.
+struct FastMem {
+    P4<double> pl[VT_TOPO_FACES];
+    uint64_t fm[VT_TOPO_FACES];            // vertices on each face
+    uint8_t next[VT_TOPO_FACES][64];       // next[f][u]: the vertex after u on face f
+    int32_t order[64];                     // the faces by ascending id
+    uint8_t loop[3 * 64];                  // the cell's loop entries
+};
+#define STRUCT_BATCH 16
+
+template <typename PT4>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) k_structure_fast(StructArgs A) {
+    __shared__ FastMem Ms[4];
+    FastMem &S = Ms[threadIdx.x >> 6];
+    const int lane = lane_id();
+    // each XCD (blocks are dealt to them in turn) takes one contiguous eighth of the Morton order
+    const int seg = (int)(blockIdx.x % VT_XCD_SEGMENTS);
+    const int64_t c_end = A.ncells * (seg + 1) / VT_XCD_SEGMENTS;
+    const int64_t step = (int64_t)(gridDim.x / VT_XCD_SEGMENTS) * 4 * STRUCT_BATCH;
+    for (int64_t c0 = A.ncells * seg / VT_XCD_SEGMENTS + ((int64_t)(blockIdx.x / VT_XCD_SEGMENTS) * 4 + (threadIdx.x >> 6)) * STRUCT_BATCH;
+         c0 < c_end; c0 += step) {
+        // the batch's scalars, a cell per lane
+        const int64_t cl = c0 + lane;
+        bool todo = lane < STRUCT_BATCH && cl < c_end;
+        if (todo) todo = A.smark[cl] == MARK_FAST;
+        int nf_l = 0, nv_l = 0, item_l = 0;
+        int64_t vb_l = 0, fb_l = 0, lb_l = 0;
+        double x_l = 0.0, y_l = 0.0, z_l = 0.0;
+        if (todo) {
+            const int32_t j0 = A.cells[cl];
+            nf_l = A.src.cnf[cl];
+            nv_l = A.src.cnv[cl];
+            const int64_t row = A.srow[j0];
+            gpos<PT4>(A.src.spos, j0, x_l, y_l, z_l);
+            item_l = item_of(A.items, A.n_items, j0);
+            vb_l = A.vert_off[row];
+            fb_l = A.face_off[row];
+            lb_l = A.loop_base[row];
+        }
+        for (uint64_t m = __ballot(todo); m; m &= m - 1) {
+            const int i = uni_i(__builtin_ctzll(m));
+            const int64_t c = c0 + i;
+            const int nf = (int)readlane_u32((uint32_t)nf_l, i), nv = (int)readlane_u32((uint32_t)nv_l, i);
+            const double sx = readlane_d(x_l, i), sy = readlane_d(y_l, i), sz = readlane_d(z_l, i);
+            const DevItem &it = A.items[(int)readlane_u32((uint32_t)item_l, i)];
+            auto readlane_i64 = [&](int64_t v) {
+                return (int64_t)(((uint64_t)readlane_u32((uint32_t)((uint64_t)v >> 32), i) << 32) |
+                                 readlane_u32((uint32_t)(uint64_t)v, i));
+            };
+            const int64_t vb = readlane_i64(vb_l), fb = readlane_i64(fb_l), lb = readlane_i64(lb_l);
+            const int32_t *rec = A.src.ctopo + c * VT_TOPO_STRIDE;
+            int32_t tag = -1, gid = 0;
+            uint32_t t = 0;
+            if (lane < nf) tag = rec[lane];
+            if (lane < nv) t = (uint32_t)rec[VT_TOPO_FACES + lane];
+            const int k[3] = {(int)(t & 0xFFu), (int)((t >> 8) & 0xFFu), (int)((t >> 16) & 0xFFu)};
+            // a record that fails a check can only come from a fault of the clip kernel (rebuild.h)
+            bool ok = true;
+            if (lane < nf) ok = tag >= 0 && (int64_t)tag < A.src.npos;
+            if (lane < nv) ok = ok && (t >> 24) == 0 && k[0] < nf && k[1] < nf && k[2] < nf && k[0] != k[1] && k[1] != k[2] && k[0] != k[2];
+            bool bad = __ballot(!ok) != 0ull;
+            double x = 0.0, y = 0.0, z = 0.0;
+            if (!bad) {
+                if (lane < nf) {
+                    double qx, qy, qz;
+                    gpos<PT4>(A.src.spos, tag, qx, qy, qz);
+                    gid = A.sgid[tag];
+                    // the expressions of rebuild.h, so the vertices are the clip kernel's own
+                    qx -= sx;
+                    qy -= sy;
+                    qz -= sz;
+                    if (it.periodic) {
+                        qx -= it.L[0] * rint(qx * (1.0 / it.L[0]));
+                        qy -= it.L[1] * rint(qy * (1.0 / it.L[1]));
+                        qz -= it.L[2] * rint(qz * (1.0 / it.L[2]));
+                    }
+                    S.pl[lane] = P4<double>{qx, qy, qz, 0.5 * (qx * qx + qy * qy + qz * qz)};
+                    S.fm[lane] = 0ull;
+                }
+                wave_sync();
+                if (lane < nv) {
+                    intersect3<double>(S.pl[k[0]], S.pl[k[1]], S.pl[k[2]], x, y, z);
+                    for (int e = 0; e < 3; ++e) atomicOr((unsigned long long *)&S.fm[k[e]], 1ull << lane);
+                }
+                bad = __ballot(!(isfinite(x) && isfinite(y) && isfinite(z))) != 0ull;
+                wave_sync();
+                // on face k[e] the next vertex also lies on the face before k[e] in the triple
+                if (lane < nv) {
+                    for (int e = 0; e < 3; ++e) {
+                        const uint64_t w = S.fm[k[e]] & S.fm[k[(e + 2) % 3]] & ~(1ull << lane);
+                        S.next[k[e]][lane] = (uint8_t)(w ? __builtin_ctzll(w) : 255);
+                    }
+                }
+            }
+            if (bad) {
+                if (lane == 0) {
+                    atomicAdd(&A.counters[CTR_REC_REJECT], 1u);
+                    atomicOr(&A.counters[CTR_STATUS], VT_DEV_TOPOLOGY);
+                }
+                continue;
+            }
+            // the faces by ascending id, then slot (k_structure's key)
+            int rank = 0;
+            const uint32_t key = (uint32_t)gid + 16u;
+            for (int q = 0; q < nf; ++q) {
+                const uint32_t g = readlane_u32(key, q);
+                rank += g < key || (g == key && q < lane) ? 1 : 0;
+            }
+            if (lane < nf) S.order[rank] = lane;
+            wave_sync();
+            const int f = lane < nf ? S.order[lane] : 0;
+            const uint64_t mf = S.fm[f];
+            const int len = lane < nf ? __popcll(mf) : 0;
+            const int32_t fid = __shfl(gid, f);
+            int total;
+            const int pre = wave_excl_scan(len, &total);
+            bool open_loop = total != 3 * nv;
+            if (lane < nf && !open_loop) {
+                const int u0 = __builtin_ctzll(mf);
+                int u = u0;
+                for (int q = 0; q < len; ++q) {
+                    S.loop[pre + q] = (uint8_t)u;
+                    u = S.next[f][u & 63];
+                }
+                open_loop = len < 3 || u != u0;
+            }
+            if (__ballot(open_loop) != 0ull) {
+                if (lane == 0) atomicOr(&A.counters[CTR_STATUS], VT_DEV_TOPOLOGY);
+                continue;
+            }
+            wave_sync();
+            if (lane < nf) {
+                A.face_nbr[fb + lane] = fid;
+                A.loop_off[fb + lane] = lb + pre;
+            }
+            if (lane < nv) {
+                double *v = A.verts + 3 * (vb + lane);
+                v[0] = sx + x;
+                v[1] = sy + y;
+                v[2] = sz + z;
+            }
+            for (int q = lane; q < total; q += 64) A.loop_vert[lb + q] = S.loop[q];
+            wave_sync();
+        }
+    }
+}
+
+// after the scans: the totals in one place for the host
+__global__ void k_structure_totals(const int64_t *vert_off, const int64_t *face_off, const int64_t *lbase, int64_t n,
+                                   int64_t *tot) {
+    if (threadIdx.x == 0) {
+        tot[0] = vert_off[n];
+        tot[1] = face_off[n];
+        tot[2] = lbase[n];
+    }
+}
+
 __global__ void k_store_last(int64_t *dst, const int64_t *src) {
     if (threadIdx.x == 0 && blockIdx.x == 0) *dst = *src;
 }
@@ -335,36 +524,33 @@ static hipError_t structure_pass(vt_ctx *c, StructArgs &a) {
     return e;
 }
 
-static hipError_t reserve_structure(vt_ctx *c) {
-    const int64_t n = c->n_owned;
-    if (c->cap_struct >= n && c->st_cnt) return hipSuccess;
-    (void)hipFree(c->st_cnt);
-    (void)hipFree(c->st_lbase);
-    (void)hipFree(c->smark);
-    (void)hipFree(c->squeue);
-    c->st_cnt = nullptr;
-    c->st_lbase = nullptr;
-    c->smark = nullptr;
-    c->squeue = nullptr;
-    c->cap_struct = 0;
-    hipError_t e = hipMalloc(&c->st_cnt, sizeof(int64_t) * 3 * (size_t)n);
-    if (e == hipSuccess) e = hipMalloc(&c->st_lbase, sizeof(int64_t) * (size_t)(n + 1));
-    if (e == hipSuccess) e = hipMalloc(&c->smark, (size_t)n);
-    if (e == hipSuccess) e = hipMalloc(&c->squeue, sizeof(int32_t) * (size_t)c->cap_retry);
-    if (e == hipSuccess) c->cap_struct = n;
-    return e;
-}
-
 void vt_struct_free(vt_ctx *c) {
     (void)hipFree(c->st_cnt);
     (void)hipFree(c->st_lbase);
+    (void)hipFree(c->st_tmp);
+    (void)hipFree(c->st_slow);
     (void)hipFree(c->smark);
     (void)hipFree(c->squeue);
-    c->st_cnt = nullptr;
-    c->st_lbase = nullptr;
+    c->st_cnt = c->st_lbase = c->st_tmp = nullptr;
+    c->st_slow = nullptr;
     c->smark = nullptr;
     c->squeue = nullptr;
     c->cap_struct = 0;
+}
+
+static hipError_t reserve_structure(vt_ctx *c) {
+    const int64_t n = c->n_owned;
+    if (c->cap_struct >= n && c->st_cnt) return hipSuccess;
+    vt_struct_free(c);
+    hipError_t e = hipMalloc(&c->st_cnt, sizeof(int64_t) * 3 * (size_t)n);
+    if (e == hipSuccess) e = hipMalloc(&c->st_lbase, sizeof(int64_t) * (size_t)(n + 1));
+    if (e == hipSuccess) e = hipMalloc(&c->st_tmp, sizeof(int64_t) * 3 * (size_t)(1 + vt_scan_tmp_elems(n)));
+    if (e == hipSuccess) e = hipMalloc(&c->st_slow, sizeof(int32_t) * (size_t)n);
+    if (e == hipSuccess) e = hipMalloc(&c->smark, (size_t)n);
+    if (e == hipSuccess) e = hipMalloc(&c->squeue, sizeof(int32_t) * (size_t)c->cap_retry);
+    if (e == hipSuccess) c->cap_struct = n;
+    else vt_struct_free(c);
+    return e;
 }
 
 // Count, scan, and (if the capacities suffice) write.  sizes[] gets the totals of vertices,
@@ -390,6 +576,7 @@ hipError_t vt_launch_structure(vt_ctx *c, int64_t *vert_off, double *verts, int6
     a.queue_cap = c->cap_retry;
     a.squeue = c->squeue;
     a.squeue_cap = c->cap_retry;
+    a.slow = c->st_slow;
     a.smark = c->smark;
     a.counters = c->counters;
     a.area_eps = c->opts.area_eps > 0 ? c->opts.area_eps : 1e-12f;
@@ -404,25 +591,33 @@ hipError_t vt_launch_structure(vt_ctx *c, int64_t *vert_off, double *verts, int6
     a.face_nbr = face_nbr;
     a.loop_off = loop_off;
     a.loop_vert = loop_vert;
-    // counts start at zero (a row no kernel reaches keeps an empty structure)
-    e = vt_launch_zero_u32((uint32_t *)c->st_cnt, 6 * n, c->stream);
+    int64_t *totals = c->st_tmp + 3 * vt_scan_tmp_elems(n);
+    e = vt_launch_zero_u32(c->counters + CTR_STRUCT_SLOW, 1, c->stream);
     if (e == hipSuccess) e = vt_launch_zero_u32(c->counters + CTR_STRUCT_Q, 1, c->stream);
-    if (e == hipSuccess) e = structure_pass(c, a);
-    if (e == hipSuccess) e = vt_launch_scan_i64(a.nvert, vert_off, n, c->scan_tmp, c->stream);
-    if (e == hipSuccess) e = vt_launch_scan_i64(a.nface, face_off, n, c->scan_tmp, c->stream);
-    if (e == hipSuccess) e = vt_launch_scan_i64(a.nloop, c->st_lbase, n, c->scan_tmp, c->stream);
     if (e != hipSuccess) return e;
+    k_structure_count<<<(unsigned)((n + 255) / 256), 256, 0, c->stream>>>(a);
+    e = hipGetLastError();
+    if (e == hipSuccess) e = structure_pass(c, a);
+    if (e == hipSuccess) e = vt_launch_scan3_i64(a.nvert, vert_off, face_off, c->st_lbase, n, c->st_tmp, c->stream);
+    if (e != hipSuccess) return e;
+    k_structure_totals<<<1, 64, 0, c->stream>>>(vert_off, face_off, c->st_lbase, n, totals);
     int64_t tot[3];
-    e = hipMemcpyAsync(&tot[0], vert_off + n, sizeof(int64_t), hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(&tot[1], face_off + n, sizeof(int64_t), hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(&tot[2], c->st_lbase + n, sizeof(int64_t), hipMemcpyDeviceToHost, c->stream);
+    e = hipMemcpyAsync(tot, totals, sizeof(tot), hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) return e;
     for (int k = 0; k < 3; ++k) sizes[k] = tot[k];
     *fits = tot[0] <= vert_cap && tot[1] <= face_cap && tot[2] <= loop_cap && verts && face_nbr && loop_off && loop_vert;
     if (!*fits) return hipSuccess;
     a.write = 1;
-    e = structure_pass(c, a);
+    int ncu = 0;
+    hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, c->device);
+    if (ncu <= 0) ncu = 256;
+    // six blocks of four wavefronts per CU, a multiple of the XCDs
+    const unsigned blocks = (unsigned)((ncu * 6 + VT_XCD_SEGMENTS - 1) / VT_XCD_SEGMENTS * VT_XCD_SEGMENTS);
+    if (c->dtype == VT_F32) k_structure_fast<float4><<<blocks, 256, 0, c->stream>>>(a);
+    else k_structure_fast<double4><<<blocks, 256, 0, c->stream>>>(a);
+    e = hipGetLastError();
+    if (e == hipSuccess) e = structure_pass(c, a);
     if (e == hipSuccess) {
         k_store_last<<<1, 64, 0, c->stream>>>(loop_off + tot[1], c->st_lbase + n);
         e = hipGetLastError();

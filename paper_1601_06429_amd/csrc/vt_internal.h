@@ -34,6 +34,7 @@
 #define CTR_DEBUG 9        // bit k set: a clip in the grid kernel returned -k (diagnostics)
 #define CTR_GRID_Q 10      // grid deposit: cells handed from the normal to the large kernel
 #define CTR_STRUCT_Q 11    // structure output: cells handed from the normal to the large kernel
+#define CTR_STRUCT_SLOW 4  // structure output: cells that need more than their record
 #define CTR_REC_REJECT 12  // topology records that failed their checks (a clip-kernel fault; 0 expected)
 #define CTR_TAB_PIECES 13  // level table: pieces of long runs listed for k_level_fill
 // Work counters of the XCD segments (fast clip kernel, grid deposit), each in a 128-byte line of its
@@ -156,9 +157,12 @@ struct vt_ctx {
     int32_t *samp_fine = nullptr;
     int64_t cap_samp = 0;
     // structure output (structure.hip): per-row counts (vertices, faces, loop entries), loop
-    // offsets per row, per-cell large-kernel marks, overflow queue
+    // offsets per row, scan scratch and totals, per-cell kernel marks, the queues of the cells that
+    // the normal and the large kernel take
     int64_t *st_cnt = nullptr;
     int64_t *st_lbase = nullptr;
+    int64_t *st_tmp = nullptr;
+    int32_t *st_slow = nullptr;
     uint8_t *smark = nullptr;
     int32_t *squeue = nullptr;
     int64_t cap_struct = 0;
@@ -175,6 +179,8 @@ hipError_t vt_launch_sort(vt_ctx *c, const void *pos, const int32_t *gid);
 hipError_t vt_launch_clip(vt_ctx *c);  // records ev[2] between the two kernels when timing
 hipError_t vt_launch_scan_i64(const int64_t *in, int64_t *out, int64_t n, int64_t *tmp, hipStream_t s);
 hipError_t vt_launch_scan_i32(const int32_t *in, int32_t *out, int64_t n, int64_t *tmp, hipStream_t s);
+hipError_t vt_launch_scan3_i64(const int64_t *in, int64_t *o0, int64_t *o1, int64_t *o2, int64_t n, int64_t *tmp,
+                               hipStream_t s);
 hipError_t vt_launch_cells(vt_ctx *c, double *volume, int64_t *nbr_off, int32_t *nbr_ids, int64_t nbr_cap,
                            uint8_t *cell_status);
 hipError_t vt_launch_density(vt_ctx *c, const void *mass, vt_dtype dt, double *rho);
