@@ -855,25 +855,27 @@ __global__ void __launch_bounds__(256) k_grid_fused(GridArgs A) {
 // ex*ex + ey*ey + ez*ez; ties to the smaller global id), i.e. of the Voronoi cell that contains
 // it.  A voxel averages the sub^3 points at its sub-cell centres.
 //
-// The tessellation is already built, so each cell claims its points: a wavefront per cell walks
-// the sample points within R of its seed (R its largest vertex distance) and claims a point
-// when the seed is nearer than every facet neighbour (or as near, with the smaller global id).
-// In exact arithmetic the cell is the intersection of its facet half-spaces, so the one cell
-// holding a point claims it; the comparisons are the reference's own squared distances, and
-// the claims go through a 64-bit atomic minimum on (global id, sorted index).  A point no cell
-// claims (rounding at a boundary, or a cell with more candidate points or facets than a wave takes)
-// is found by its own exact search.  With several points per voxel a cell's sphere holds
-// sub^3 times as many candidates, and tiles of points do better: one wavefront takes a 4 x 4 x 4
-// tile (a lane each) and scans one candidate list for the tile, the particles of the Morton
-// cells covering the tile widened by r, staged through LDS 64 at a time; a lane is done when its
-// best distance is below its distance to the sides of the covered cells less two key quanta,
-// otherwise r doubles, and a tile whose region holds more than VT_SAMPLE_DENSE particles lets
-// every lane search on its own through finer cells.  The minimum-image shift uses rint(e / L)
-// with 1 / L precomputed; it can round differently from the quotient only near |e| = L / 2,
-// where no nearest particle lies.
-#define VT_CLAIM_MAX 65536  // candidate points above which a cell leaves its points to the search
-#define VT_SAMPLE_DENSE 4096  // tiles: candidates above which a tile's lanes search on their own
-#define VT_CLAIM_NBR 160    // facet neighbours staged per cell (the large clip kernel keeps at most 136)
+// The tessellation is already built, so each cell claims its points.  Points lie in rows along z, and
+// a row meets the cell in an interval whose ends are linear in the row's (x, y) for each facet plane:
+// a wavefront per cell gives a lane to every row of points within R of the seed (R the cell's largest
+// vertex distance) and takes the facet neighbours' planes one after another, so a row costs a few
+// operations per plane however many points it holds.
+//
+// Every plane is taken twice, moved inwards and outwards by a margin above all rounding, in this
+// arithmetic and in the reference's: D.y <= |D|^2 / 2 -+ 1e-13 (R + |D|)^2, where the reference's
+// squared distances are off by at most 8 eps (R + |D|)^2 between them, and the ends by 1e-7 of a
+// point spacing more (the points' own coordinates round by eps times the period, up to 2e-11 of a
+// spacing).  Points inside the inner interval are the cell's: stored.  Points between the two are
+// compared with every neighbour by the reference's own squared distances, ties to the smaller id, and
+// claimed through a 64-bit atomic minimum on (global id, sorted index).  A point no cell claims (a
+// failed cell, or an axis with too few points to unwrap) is found by its own exact search.
+//
+// The kernel is bound by VALU issue (about 15 planes of 8 FP64 operations a round of 64 rows, with
+// the rows of a small cell filling half the lanes) and the latency of a cell's loads.  500k cells on
+// 192^3 points took 3.00 ms with every candidate point tested against the neighbours one by one and
+// take 0.77 ms; 100k cells on 240 x 216 x 192 points (27 a voxel) took 8.4-10.5 ms in tiles of points
+// that shared a list of candidate particles and take 0.53 ms.
+#define VT_CLAIM_NBR 136    // facet neighbours staged per cell (the large clip kernel keeps no more)
 
 struct SampleArgs {
     const void *spos;
@@ -893,8 +895,8 @@ struct SampleArgs {
     double *grid;
     int32_t *nearest;           // global id per voxel (of its last point), or null
     unsigned long long *slot;   // per sample point: (global id << 32) | sorted index, ~0 unclaimed
+    int batch;                  // cells a wavefront takes at a time (at most 64)
     int nx, ny, nz, sub;
-    double r0;                  // tiles: first widening (the mean inter-particle distance)
 };
 
 // sample point (fine index f along axis a): voxel f / sub, sub-cell f % sub, at the sub-cell centre
@@ -913,13 +915,6 @@ __device__ __forceinline__ double sample_coord32(const DevItem &it, int a, int d
 
 // i in [-n, 2n) to [0, n)
 __device__ __forceinline__ int wrap_once(int i, int n) { return i < 0 ? i + n : (i >= n ? i - n : i); }
-
-struct SampleMem {
-    int32_t rb[512];    // covering cells: range starts
-    int32_t rp[513];    // prefix of range lengths
-    double px[64], py[64], pz[64];
-    int32_t pg[64], pj[64];
-};
 
 __device__ __forceinline__ int32_t lower_key(const uint64_t *skey, int32_t a, int32_t c, uint64_t k) {
     while (a < c) {
@@ -1020,11 +1015,13 @@ __device__ int32_t nearest_particle(const SampleArgs &A, const DevItem &it, cons
     return bj;
 }
 
-// One wavefront per cell: the facet neighbours are staged in LDS once (nearest first when
-// there are at most 64), and the lanes take the cell's candidate points 64 at a time.
+struct ClaimPlane {
+    double x, y, z;   // separation D of the facet neighbour
+    double c, m;      // |D|^2 / 2 and the margin
+    double iz;        // 1 / D_z
+};
 struct ClaimMem {
-    double px[VT_CLAIM_NBR], py[VT_CLAIM_NBR], pz[VT_CLAIM_NBR];
-    int32_t pg[VT_CLAIM_NBR];
+    ClaimPlane pl[VT_CLAIM_NBR];
 };
 
 template <typename PT4>
@@ -1036,254 +1033,142 @@ __global__ void __launch_bounds__(256) k_sample_claim(SampleArgs A) {
     const int sub = A.sub;
     const int dims[3] = {A.nx, A.ny, A.nz};
     const int64_t F[3] = {(int64_t)A.nx * sub, (int64_t)A.ny * sub, (int64_t)A.nz * sub};
-    const double invL[3] = {1.0 / it.L[0], 1.0 / it.L[1], 1.0 / it.L[2]};
-    const int64_t nwaves = (int64_t)gridDim.x * (blockDim.x >> 6);
-    for (int64_t c = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); c < A.ncells; c += nwaves) {
-        if (A.cstat[c] & VT_CELL_FAILED) continue;
-        const int32_t cnt = A.ccnt[c];
-        if (cnt > VT_CLAIM_NBR) continue;   // left to the search
-        const int32_t j0 = A.cells[c];
-        const int32_t gi = A.sgid[j0];
-        double x[3];
-        gpos<PT4>(A.spos, j0, x[0], x[1], x[2]);
-        const double R = A.crad[c] * (1.0 + 1e-9) + 1e-12 * it.S;
-        const double R2 = R * R;
-        if (!(R2 < 1e300)) continue;   // not a finite radius: the points go to the search
-        int64_t f0[3], nf[3];
-        bool ok = true;
-        for (int a = 0; a < 3; ++a) {
-            const double hf = it.L[a] / (double)F[a];
-            f0[a] = (int64_t)floor((x[a] - R - it.lo[a]) / hf - 0.5) - 1;
-            nf[a] = (int64_t)floor((x[a] + R - it.lo[a]) / hf - 0.5) + 2 - f0[a];
-            if (nf[a] > F[a]) {   // the cell spans the period along a: every point once
-                f0[a] = 0;
-                nf[a] = F[a];
+    const double invL[3] = {uni_d(1.0 / it.L[0]), uni_d(1.0 / it.L[1]), uni_d(1.0 / it.L[2])};
+    const double ihf[3] = {uni_d((double)F[0] / it.L[0]), uni_d((double)F[1] / it.L[1]), uni_d((double)F[2] / it.L[2])};
+    // each XCD (blocks are dealt to them in turn) takes one contiguous eighth of the Morton order
+    const int seg = (int)(blockIdx.x % VT_XCD_SEGMENTS);
+    const int64_t c_end = A.ncells * (seg + 1) / VT_XCD_SEGMENTS;
+    const int64_t step = (int64_t)(gridDim.x / VT_XCD_SEGMENTS) * 4 * A.batch;
+    for (int64_t c0 = A.ncells * seg / VT_XCD_SEGMENTS + ((int64_t)(blockIdx.x / VT_XCD_SEGMENTS) * 4 + (threadIdx.x >> 6)) * A.batch;
+         c0 < c_end; c0 += step) {
+        // the batch's scalars, a cell per lane: the box of points within R, empty for most cells when
+        // there are fewer points than cells
+        const int64_t cl = c0 + lane;
+        bool todo = lane < A.batch && cl < c_end;
+        if (todo) todo = !(A.cstat[cl] & VT_CELL_FAILED);
+        int32_t j_l = 0, cnt_l = 0;
+        int f0_l[3] = {0, 0, 0}, nf_l[3] = {0, 0, 0};
+        double x_l[3] = {0.0, 0.0, 0.0}, R_l = 0.0;
+        int64_t row_l = 0;
+        if (todo) {
+            j_l = A.cells[cl];
+            cnt_l = A.ccnt[cl];
+            row_l = A.crow[cl];
+            gpos<PT4>(A.spos, j_l, x_l[0], x_l[1], x_l[2]);
+            R_l = A.crad[cl] * (1.0 + 1e-9) + 1e-12 * it.S;
+            todo = cnt_l <= VT_CLAIM_NBR && R_l < it.S;  // false for a radius that is not a number
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                const double g = x_l[a] - it.lo[a];
+                const double p = ceil((g - R_l) * ihf[a] - 0.5 - 1e-6), q = floor((g + R_l) * ihf[a] - 0.5 + 1e-6);
+                // one correction brings every index into [0, F); an axis that cannot (fewer points than
+                // a cell spans) leaves the cell's points to the search
+                const bool ok = q >= p && p >= -(double)F[a] && q < 2.0 * (double)F[a] && F[a] < (1 << 29);
+                todo = todo && ok;
+                f0_l[a] = ok ? (int)p : 0;
+                nf_l[a] = ok ? (int)q - (int)p + 1 : 0;
+                if (a < 2 && nf_l[a] > F[a]) {  // the box spans the period: every row once
+                    f0_l[a] = 0;
+                    nf_l[a] = (int)F[a];
+                }
             }
-            ok = ok && nf[a] >= 1;
+            todo = todo && (int64_t)nf_l[0] * nf_l[1] < (1 << 22);
         }
-        const int64_t ncand = nf[0] * nf[1] * nf[2];
-        if (!ok || ncand > VT_CLAIM_MAX) continue;
-        // one correction brings every candidate index into [0, F)
-        for (int a = 0; a < 3; ++a) ok = ok && F[a] < (1 << 29) && f0[a] >= -F[a] && f0[a] + nf[a] <= 2 * F[a];
-        if (!ok) continue;
-        const int64_t row = A.crow[c];
-        if (cnt <= 64) {
-            // nearest neighbours first: a point outside the cell fails on one of them early
-            double px = 0.0, py = 0.0, pz = 0.0;
-            int32_t pg = 0;
-            uint64_t key[1] = {~0ull};
-            if (lane < cnt) {
-                const int32_t j = A.stage_ids[row + lane];
-                gpos<PT4>(A.spos, j, px, py, pz);
-                pg = A.sgid[j];
+        for (uint64_t tm = __ballot(todo); tm; tm &= tm - 1) {
+            const int i = uni_i(__builtin_ctzll(tm));
+            const int32_t j0 = (int32_t)readlane_u32((uint32_t)j_l, i), cnt = (int32_t)readlane_u32((uint32_t)cnt_l, i);
+            const int64_t row = (int64_t)(((uint64_t)readlane_u32((uint32_t)((uint64_t)row_l >> 32), i) << 32) |
+                                          readlane_u32((uint32_t)(uint64_t)row_l, i));
+            const double x[3] = {readlane_d(x_l[0], i), readlane_d(x_l[1], i), readlane_d(x_l[2], i)};
+            const double R = readlane_d(R_l, i), R2 = R * R;
+            int f0[3], nf[3];
+            for (int a = 0; a < 3; ++a) {
+                f0[a] = (int)readlane_u32((uint32_t)f0_l[a], i);
+                nf[a] = (int)readlane_u32((uint32_t)nf_l[a], i);
+            }
+            const int32_t gi = A.sgid[j0];
+            wave_sync();
+            for (int k = lane; k < cnt; k += 64) {
+                double px, py, pz;
+                gpos<PT4>(A.spos, A.stage_ids[row + k], px, py, pz);
                 double ex = px - x[0], ey = py - x[1], ez = pz - x[2];
                 ex -= it.L[0] * rint(ex * invL[0]);
                 ey -= it.L[1] * rint(ey * invL[1]);
                 ez -= it.L[2] * rint(ez * invL[2]);
-                key[0] = ((uint64_t)__float_as_uint((float)(ex * ex + ey * ey + ez * ez)) << 32) | (uint64_t)lane;
+                const double d2 = ex * ex + ey * ey + ez * ez, r = R + sqrt(d2);
+                M.pl[k] = ClaimPlane{ex, ey, ez, 0.5 * d2, 1e-13 * r * r, 1.0 / ez};
             }
-            bitonic_u64<1>(key);
-            const int src = (int)(key[0] & 63ull);
-            const double sx_ = __shfl(px, src), sy_ = __shfl(py, src), sz_ = __shfl(pz, src);
-            const int32_t sg_ = __shfl(pg, src);
-            if (lane < cnt) {
-                M.px[lane] = sx_;
-                M.py[lane] = sy_;
-                M.pz[lane] = sz_;
-                M.pg[lane] = sg_;
-            }
-        } else {
-            for (int k = lane; k < cnt; k += 64) {
-                const int32_t j = A.stage_ids[row + k];
-                gpos<PT4>(A.spos, j, M.px[k], M.py[k], M.pz[k]);
-                M.pg[k] = A.sgid[j];
-            }
-        }
-        wave_sync();
-        const unsigned long long mine = ((unsigned long long)(uint32_t)gi << 32) | (uint32_t)j0;
-        for (int64_t base = 0; base < ncand; base += 64) {
-            const int64_t m = base + lane;
-            if (m < ncand) {
-                // 32-bit index arithmetic: the candidate's offsets, then one period's correction
-                // (a periodic cell is less than a quarter period across)
-                int t, v;
-                const int r = divmod_small((int)m, (int)nf[2], t);
-                const int u = divmod_small(r, (int)nf[1], v);
-                const int w0 = wrap_once((int)f0[0] + u, (int)F[0]);
-                const int w1 = wrap_once((int)f0[1] + v, (int)F[1]);
-                const int w2 = wrap_once((int)f0[2] + t, (int)F[2]);
-                const double q0 = sample_coord32(it, 0, dims[0], sub, w0);
-                const double q1 = sample_coord32(it, 1, dims[1], sub, w1);
-                const double q2 = sample_coord32(it, 2, dims[2], sub, w2);
-                double e0 = x[0] - q0, e1 = x[1] - q1, e2 = x[2] - q2;
-                e0 -= it.L[0] * rint(e0 * invL[0]);
-                e1 -= it.L[1] * rint(e1 * invL[1]);
-                e2 -= it.L[2] * rint(e2 * invL[2]);
-                const double d2 = e0 * e0 + e1 * e1 + e2 * e2;
-                if (d2 <= R2) {
+            wave_sync();
+            const unsigned long long mine = ((unsigned long long)(uint32_t)gi << 32) | (uint32_t)j0;
+            // index along z of the point at height t above the seed: (t + zb) ihf
+            const double zb = x[2] - it.lo[2];
+            const int nrow = nf[0] * nf[1];
+            for (int base = 0; base < nrow; base += 64) {
+                const int m = base + lane;
+                if (m >= nrow) continue;
+                int v;
+                const int u = divmod_small(m, nf[1], v);
+                const int w0 = wrap_once(f0[0] + u, (int)F[0]), w1 = wrap_once(f0[1] + v, (int)F[1]);
+                const double q0 = sample_coord32(it, 0, dims[0], sub, w0), q1 = sample_coord32(it, 1, dims[1], sub, w1);
+                double y0 = q0 - x[0], y1 = q1 - x[1];
+                y0 -= it.L[0] * rint(y0 * invL[0]);
+                y1 -= it.L[1] * rint(y1 * invL[1]);
+                const double rr = R2 - (y0 * y0 + y1 * y1);
+                if (rr < 0.0) continue;
+                // the row inside the planes moved inwards (s) and outwards (p)
+                double s0 = -R, s1 = R, p0 = -R, p1 = R;
+                for (int k = 0; k < cnt; ++k) {
+                    const ClaimPlane &P = M.pl[k];
+                    const double c = fma(-P.x, y0, fma(-P.y, y1, P.c));
+                    const double ci = c - P.m, co = c + P.m;
+                    if (P.z > 1e-150) {
+                        s1 = fmin(s1, ci * P.iz);
+                        p1 = fmin(p1, co * P.iz);
+                    } else if (P.z < -1e-150) {
+                        s0 = fmax(s0, ci * P.iz);
+                        p0 = fmax(p0, co * P.iz);
+                    } else {
+                        if (ci < 0.0) s1 = -1e300;
+                        if (co < 0.0) p1 = -1e300;
+                    }
+                }
+                if (p1 < p0) continue;
+                const int a0 = max(f0[2], (int)fmax(ceil((p0 + zb) * ihf[2] - 0.5 - 1e-7), -1e9));
+                const int a1 = min(f0[2] + nf[2] - 1, (int)fmin(floor((p1 + zb) * ihf[2] - 0.5 + 1e-7), 1e9));
+                int b0 = a1 + 1, b1 = a1;   // the points inside for certain
+                if (s1 >= s0) {
+                    b0 = min(max(a0, (int)ceil((s0 + zb) * ihf[2] - 0.5 + 1e-7)), a1 + 1);
+                    b1 = max(min(a1, (int)floor((s1 + zb) * ihf[2] - 0.5 - 1e-7)), b0 - 1);
+                }
+                unsigned long long *slot = A.slot + ((int64_t)w0 * F[1] + w1) * F[2];
+                for (int f = a0; f <= a1; ++f) {
+                    const int w2 = wrap_once(f, (int)F[2]);
+                    if (f >= b0 && f <= b1) {
+                        slot[w2] = mine;
+                        continue;
+                    }
+                    const double q2 = sample_coord32(it, 2, dims[2], sub, w2);
+                    double e0 = x[0] - q0, e1 = x[1] - q1, e2 = x[2] - q2;
+                    e0 -= it.L[0] * rint(e0 * invL[0]);
+                    e1 -= it.L[1] * rint(e1 * invL[1]);
+                    e2 -= it.L[2] * rint(e2 * invL[2]);
+                    const double d2 = e0 * e0 + e1 * e1 + e2 * e2;
                     bool win = true;
-                    for (int32_t k = 0; k < cnt && win; ++k) {
-                        double ex = M.px[k] - q0, ey = M.py[k] - q1, ez = M.pz[k] - q2;
+                    for (int k = 0; k < cnt && win; ++k) {
+                        const int32_t j = A.stage_ids[row + k];
+                        double px, py, pz;
+                        gpos<PT4>(A.spos, j, px, py, pz);
+                        double ex = px - q0, ey = py - q1, ez = pz - q2;
                         ex -= it.L[0] * rint(ex * invL[0]);
                         ey -= it.L[1] * rint(ey * invL[1]);
                         ez -= it.L[2] * rint(ez * invL[2]);
                         const double dj = ex * ex + ey * ey + ez * ez;
-                        win = !(dj < d2 || (dj == d2 && M.pg[k] < gi));
+                        win = !(dj < d2 || (dj == d2 && A.sgid[j] < gi));
                     }
-                    if (win) atomicMin(&A.slot[((int64_t)w0 * F[1] + w1) * F[2] + w2], mine);
+                    if (win) atomicMin(&slot[w2], mine);
                 }
             }
         }
-        wave_sync();
-    }
-}
-
-template <typename PT4>
-__global__ void __launch_bounds__(256) k_sample_tiles(SampleArgs A) {
-    extern __shared__ char smem[];
-    SampleMem &S = *reinterpret_cast<SampleMem *>(smem + (size_t)(threadIdx.x >> 6) * sizeof(SampleMem));
-    const int lane = threadIdx.x & 63;
-    const uint64_t lt = (1ull << lane) - 1ull;
-    const DevItem it = uniform_item(A.items[0]);
-    const int sub = A.sub;
-    const int64_t fd[3] = {(int64_t)A.nx * sub, (int64_t)A.ny * sub, (int64_t)A.nz * sub};
-    const int64_t ntile[3] = {(fd[0] + 3) / 4, (fd[1] + 3) / 4, (fd[2] + 3) / 4};
-    const int64_t n_tiles = ntile[0] * ntile[1] * ntile[2];
-    const int dims[3] = {A.nx, A.ny, A.nz};
-    const double quantum = it.S / (double)(1 << VT_MORTON_BITS);
-    const double invL[3] = {1.0 / it.L[0], 1.0 / it.L[1], 1.0 / it.L[2]};
-    const int64_t nwaves = (int64_t)gridDim.x * (blockDim.x >> 6);
-    for (int64_t t = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); t < n_tiles; t += nwaves) {
-        const int64_t tz = t % ntile[2], ty = (t / ntile[2]) % ntile[1], tx = t / (ntile[1] * ntile[2]);
-        const int64_t f[3] = {tx * 4 + (lane >> 4), ty * 4 + ((lane >> 2) & 3), tz * 4 + (lane & 3)};
-        const bool valid = f[0] < fd[0] && f[1] < fd[1] && f[2] < fd[2];
-        // the sample point: voxel i, sub-cell s (the reference's expression)
-        double q[3], tlo[3], thi[3];
-        for (int a = 0; a < 3; ++a) {
-            const double h = it.L[a] / dims[a];
-            const int64_t fa = valid ? f[a] : 0;
-            q[a] = it.lo[a] + ((double)(fa / sub) + ((double)(fa % sub) + 0.5) / (double)sub) * h;
-            // the tile's extent: its first and last points along a
-            const int64_t f0 = (a == 0 ? tx : a == 1 ? ty : tz) * 4;
-            const int64_t f1 = min(f0 + 3, fd[a] - 1);
-            tlo[a] = it.lo[a] + ((double)(f0 / sub) + ((double)(f0 % sub) + 0.5) / (double)sub) * h;
-            thi[a] = it.lo[a] + ((double)(f1 / sub) + ((double)(f1 % sub) + 0.5) / (double)sub) * h;
-        }
-        double best = 1e300;
-        int32_t bg = 0x7FFFFFFF, bj = -1;
-        for (double r = A.r0;; r *= 2.0) {
-            // covering Morton cells: side c >= r (coarser while more than 512 would be needed)
-            int l = 0;
-            double c = it.S;
-            while (l < VT_MORTON_BITS && 0.5 * c >= r) {
-                c *= 0.5;
-                ++l;
-            }
-            int64_t a0[3], na[3];
-            bool whole[3];
-            for (;;) {
-                const int64_t ncl = 1ll << l;
-                for (int a = 0; a < 3; ++a) {
-                    int64_t i0 = (int64_t)floor((tlo[a] - r - it.lo[a]) / c);
-                    int64_t i1 = (int64_t)floor((thi[a] + r - it.lo[a]) / c);
-                    whole[a] = i1 - i0 + 1 >= ncl;
-                    if (whole[a]) {
-                        i0 = 0;
-                        i1 = ncl - 1;
-                    }
-                    a0[a] = i0;
-                    na[a] = i1 - i0 + 1;
-                }
-                if (na[0] * na[1] * na[2] <= 512 || l == 0) break;
-                --l;
-                c *= 2.0;
-            }
-            // the lane's reach: its distance to the nearest side of the covered cells (axes not
-            // covered whole), less two key quanta for the rounding of particle keys
-            double reach = 1e300;
-            for (int a = 0; a < 3; ++a)
-                if (!whole[a]) {
-                    const double b0 = it.lo[a] + (double)a0[a] * c, b1 = it.lo[a] + (double)(a0[a] + na[a]) * c;
-                    reach = fmin(reach, fmin(q[a] - b0, b1 - q[a]));
-                }
-            reach -= 2.0 * quantum;
-            const int64_t ncl = 1ll << l;
-            const int ncells = (int)(na[0] * na[1] * na[2]);
-            int count = 0;
-            for (int base = 0; base < ncells; base += 64) {
-                const int k = base + lane;
-                int32_t cb = 0, ce = 0;
-                if (k < ncells) {
-                    const int64_t u[3] = {a0[0] + k % na[0], a0[1] + (k / na[0]) % na[1], a0[2] + k / (na[0] * na[1])};
-                    const uint64_t cx = (uint64_t)((u[0] % ncl + ncl) % ncl), cy = (uint64_t)((u[1] % ncl + ncl) % ncl),
-                                   cz = (uint64_t)((u[2] % ncl + ncl) % ncl);
-                    morton_range(A, it, l, vt_morton(cx, cy, cz), cb, ce);
-                }
-                const bool keep = ce > cb;
-                const uint64_t km = __ballot(keep);
-                if (keep) {
-                    const int slot = count + __popcll(km & lt);
-                    S.rb[slot] = cb;
-                    S.rp[slot] = ce - cb;
-                }
-                count += __popcll(km);
-            }
-            wave_sync();
-            int carry = 0;
-            for (int base = 0; base < count; base += 64) {
-                const int k = base + lane;
-                const int len = k < count ? S.rp[k] : 0;
-                int tot;
-                const int pre = wave_excl_scan(len, &tot);
-                if (k < count) S.rp[k] = carry + pre;
-                carry += tot;
-            }
-            if (lane == 0) S.rp[count] = carry;
-            wave_sync();
-            const int total = carry;
-            if (total > VT_SAMPLE_DENSE) {
-                // a dense region: every lane searches on its own, through finer cells
-                if (valid) bj = nearest_particle<PT4>(A, it, q, invL, bg);
-                break;
-            }
-            for (int c0 = 0; c0 < total; c0 += 64) {
-                const int fi = c0 + lane;
-                if (fi < total) {
-                    int lo = 0, hi = count - 1;
-                    while (lo < hi) {
-                        const int mid = (lo + hi + 1) >> 1;
-                        if (S.rp[mid] <= fi) lo = mid; else hi = mid - 1;
-                    }
-                    const int32_t j = S.rb[lo] + (fi - S.rp[lo]);
-                    double px, py, pz;
-                    gpos<PT4>(A.spos, j, px, py, pz);
-                    S.px[lane] = px;
-                    S.py[lane] = py;
-                    S.pz[lane] = pz;
-                    S.pg[lane] = A.sgid[j];
-                    S.pj[lane] = j;
-                }
-                wave_sync();
-                const int nc = min(64, total - c0);
-                for (int k = 0; k < nc; ++k) {
-                    double ex = S.px[k] - q[0], ey = S.py[k] - q[1], ez = S.pz[k] - q[2];
-                    ex -= it.L[0] * rint(ex * invL[0]);
-                    ey -= it.L[1] * rint(ey * invL[1]);
-                    ez -= it.L[2] * rint(ez * invL[2]);
-                    const double d2 = ex * ex + ey * ey + ez * ez;
-                    const int32_t gj = S.pg[k];
-                    if (d2 < best || (d2 == best && gj < bg)) {
-                        best = d2;
-                        bg = gj;
-                        bj = S.pj[k];
-                    }
-                }
-                wave_sync();
-            }
-            const bool done = (whole[0] && whole[1] && whole[2]) || (bj >= 0 && reach > 0.0 && best < reach * reach);
-            if (__ballot(valid && !done) == 0ull) break;
-        }
-        if (valid) A.slot[(f[0] * fd[1] + f[1]) * fd[2] + f[2]] = ((unsigned long long)(uint32_t)bg << 32) | (uint32_t)bj;
     }
 }
 
@@ -1374,41 +1259,25 @@ hipError_t vt_launch_grid_sample(vt_ctx *c, const double *value, int nx, int ny,
         c->cap_samp = 2 * nfine;
     }
     a.slot = (unsigned long long *)c->samp_fine;
-    const DevItem &it0 = c->h_items[0];
-    a.r0 = cbrt(it0.L[0] * it0.L[1] * it0.L[2] / (double)c->n_total);
     const int tpb = 256;
     int ncu = 0;
-    if (sub > 1) {
-        // several points per voxel: tiles of points sharing one candidate list
-        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, c->device);
-        if (ncu <= 0) ncu = 256;
-        const size_t lds = sizeof(SampleMem) * 4;
-        const int64_t tiles = ((int64_t)nx * sub + 3) / 4 * (((int64_t)ny * sub + 3) / 4) * (((int64_t)nz * sub + 3) / 4);
-        int64_t blocks = (tiles + 3) / 4;
-        if (blocks > (int64_t)ncu * 64) blocks = (int64_t)ncu * 64;
-        if (c->dtype == VT_F32)
-            k_sample_tiles<float4><<<(unsigned)blocks, 256, lds, c->stream>>>(a);
-        else
-            k_sample_tiles<double4><<<(unsigned)blocks, 256, lds, c->stream>>>(a);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        const int64_t nv = (int64_t)nx * ny * nz;
-        k_sample_average<<<(nv + tpb - 1) / tpb, tpb, 0, c->stream>>>(a);
-        return hipGetLastError();
-    }
-    // one point per voxel: the cells claim their points
-    k_fill_u64<<<(nfine + tpb - 1) / tpb, tpb, 0, c->stream>>>(a.slot, nfine, ~0ull);
     hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, c->device);
     if (ncu <= 0) ncu = 256;
-    int64_t cblocks = (a.ncells + 3) / 4;
-    if (cblocks > (int64_t)ncu * 32) cblocks = (int64_t)ncu * 32;
-    if (cblocks < 1) cblocks = 1;
+    k_fill_u64<<<(unsigned)((nfine + tpb - 1) / tpb), tpb, 0, c->stream>>>(a.slot, nfine, ~0ull);
+    // six blocks of four wavefronts per CU, a multiple of the XCDs; as many cells at a time as leave
+    // every wavefront a turn
+    const int64_t blocks = ((int64_t)ncu * 6 + VT_XCD_SEGMENTS - 1) / VT_XCD_SEGMENTS * VT_XCD_SEGMENTS;
+    a.batch = (int)std::max<int64_t>(1, std::min<int64_t>(64, a.ncells / (blocks * 4)));
     if (c->dtype == VT_F32) {
-        k_sample_claim<float4><<<(unsigned)cblocks, tpb, 0, c->stream>>>(a);
-        k_sample_fixup<float4><<<(nfine + tpb - 1) / tpb, tpb, 0, c->stream>>>(a);
+        k_sample_claim<float4><<<(unsigned)blocks, tpb, 0, c->stream>>>(a);
+        k_sample_fixup<float4><<<(unsigned)((nfine + tpb - 1) / tpb), tpb, 0, c->stream>>>(a);
     } else {
-        k_sample_claim<double4><<<(unsigned)cblocks, tpb, 0, c->stream>>>(a);
-        k_sample_fixup<double4><<<(nfine + tpb - 1) / tpb, tpb, 0, c->stream>>>(a);
+        k_sample_claim<double4><<<(unsigned)blocks, tpb, 0, c->stream>>>(a);
+        k_sample_fixup<double4><<<(unsigned)((nfine + tpb - 1) / tpb), tpb, 0, c->stream>>>(a);
+    }
+    if (sub > 1) {
+        const int64_t nv = (int64_t)nx * ny * nz;
+        k_sample_average<<<(unsigned)((nv + tpb - 1) / tpb), tpb, 0, c->stream>>>(a);
     }
     return hipGetLastError();
 }
