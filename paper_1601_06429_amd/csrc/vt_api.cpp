@@ -5,63 +5,105 @@
 #include <string.h>
 
 #include <algorithm>
+#include <type_traits>
 #include <vector>
 
 #include "vt_internal.h"
 
 namespace {
 
-template <typename T>
-hipError_t dalloc(T **p, int64_t n) {
-    *p = nullptr;
-    if (n <= 0) n = 1;
-    return hipMalloc((void **)p, sizeof(T) * (size_t)n);
-}
+// The build's scratch is one device allocation and one pinned one, divided here: thirty separate
+// ones took longer than the clip of 262k cells when a program makes a context per call.
+struct BuildSizes {
+    int64_t total, owned, tab, items, hist, scan, retry;
+    bool faces;
+};
 
-template <typename T>
-void dfree(T *&p) {
-    if (p) hipFree((void *)p);
-    p = nullptr;
+// sets the context's scratch pointers into the allocations (null: to null); returns the bytes needed
+void lay_out(vt_ctx *c, const BuildSizes &z, char *dev, char *host, size_t *dev_bytes, size_t *host_bytes) {
+    size_t off = 0;
+    char *base = dev;
+    auto put = [&](auto *&p, int64_t n) {
+        using T = std::remove_reference_t<decltype(*p)>;
+        off = (off + 255) & ~(size_t)255;
+        p = base ? (T *)(base + off) : nullptr;
+        off += sizeof(T) * (size_t)std::max<int64_t>(n, 1);
+    };
+    const int64_t NT = z.total, NO = z.owned, slots = NO * VT_FSTRIDE_FAST + z.retry * VT_FSTRIDE_BIG;
+    put(c->counters, CTR_COUNT);
+    put(c->items, z.items);
+    for (int k = 0; k < 2; ++k) {
+        put(c->keys[k], NT + 1);
+        put(c->vals[k], NT + 1);
+    }
+    put(c->hist, z.hist);
+    put(c->scan_tmp, z.scan);
+    double4 *spos = nullptr;  // for either position dtype
+    put(spos, NT);
+    c->spos = spos;
+    put(c->sgid, NT);
+    put(c->srow, NT);
+    put(c->sorig, NT);
+    put(c->tab, z.tab);
+    put(c->cells, NO);
+    put(c->row2cell, NO);
+    put(c->cvol, NO);
+    put(c->crad, NO);
+    put(c->ccnt, NO);
+    put(c->crow, NO);
+    put(c->cstat, NO);
+    put(c->cnv, NO);
+    put(c->cnp, NO);
+    put(c->cnt, NO);
+    put(c->ctopo, NO * VT_TOPO_STRIDE);
+    put(c->cnf, NO);
+    put(c->stage_ids, slots);
+    c->stage_area = c->stage_cen = nullptr;
+    if (z.faces) {
+        put(c->stage_area, slots);
+        put(c->stage_cen, 3 * slots);
+    }
+    put(c->queue, z.retry);
+    put(c->gqueue, z.retry);
+    put(c->rowoff, NO + 1);
+    *dev_bytes = off;
+    off = 0;
+    base = host;
+    put(c->h_items, z.items);
+    put(c->h_counters, CTR_COUNT);
+    *host_bytes = off;
 }
 
 void free_all(vt_ctx *c) {
-    dfree(c->items);
-    if (c->h_items) hipHostFree(c->h_items);
-    c->h_items = nullptr;
-    if (c->h_counters) hipHostFree(c->h_counters);
-    c->h_counters = nullptr;
-    for (int k = 0; k < 2; ++k) {
-        dfree(c->keys[k]);
-        dfree(c->vals[k]);
-    }
-    dfree(c->hist);
-    dfree(c->scan_tmp);
-    dfree(c->spos);
-    dfree(c->sgid);
-    dfree(c->srow);
-    dfree(c->sorig);
-    dfree(c->tab);
-    dfree(c->cells);
-    dfree(c->cvol);
-    dfree(c->crad);
-    dfree(c->ccnt);
-    dfree(c->crow);
-    dfree(c->cstat);
-    dfree(c->cnv);
-    dfree(c->cnp);
-    dfree(c->cnt);
-    dfree(c->ctopo);
-    dfree(c->cnf);
-    dfree(c->stage_ids);
-    dfree(c->stage_area);
-    dfree(c->stage_cen);
-    dfree(c->queue);
-    dfree(c->gqueue);
-    dfree(c->counters);
-    dfree(c->rowoff);
-    dfree(c->row2cell);
+    if (c->slab) hipFree(c->slab);
+    if (c->h_slab) hipHostFree(c->h_slab);
+    c->slab = c->h_slab = nullptr;
+    size_t d, h;
+    lay_out(c, BuildSizes{}, nullptr, nullptr, &d, &h);
+    c->skey = nullptr;
     c->cap_total = c->cap_owned = c->cap_tab = c->cap_retry = c->cap_items = c->cap_hist = c->cap_scan = 0;
     c->cap_faces = false;
+}
+
+hipError_t alloc_all(vt_ctx *c, const BuildSizes &z) {
+    size_t d, h;
+    lay_out(c, z, nullptr, nullptr, &d, &h);
+    hipError_t e = hipMalloc(&c->slab, d);
+    if (e == hipSuccess) e = hipHostMalloc(&c->h_slab, h, hipHostMallocDefault);
+    if (e != hipSuccess) {
+        free_all(c);
+        return e;
+    }
+    lay_out(c, z, (char *)c->slab, (char *)c->h_slab, &d, &h);
+    c->cap_total = z.total;
+    c->cap_owned = z.owned;
+    c->cap_tab = z.tab;
+    c->cap_items = z.items;
+    c->cap_hist = z.hist;
+    c->cap_scan = z.scan;
+    c->cap_retry = z.retry;
+    c->cap_faces = z.faces;
+    return hipSuccess;
 }
 
 vt_status hip_fail(hipError_t e, const char *what, int line) {
@@ -192,53 +234,21 @@ vt_status vt_build(vt_ctx **pctx, const void *pos, vt_dtype dtype, const int32_t
                        n_items > c->cap_items || hist_need > c->cap_hist || scan_need > c->cap_scan ||
                        (need_faces && !c->cap_faces);
     if (realloc_all) {
+        // No size shrinks: builds of different shapes on one context in turn (a decomposition's passes:
+        // many owned particles, then few with wider buffers) would each find another size too small.
+        const BuildSizes need{n_total, n_owned, tab_total, n_items, hist_need, scan_need, retry_need, need_faces};
+        BuildSizes grown{std::max(n_total, c->cap_total),     std::max(n_owned, c->cap_owned),
+                         std::max(tab_total, c->cap_tab),     std::max<int64_t>(n_items, c->cap_items),
+                         std::max(hist_need, c->cap_hist),    std::max(scan_need, c->cap_scan),
+                         std::max(retry_need, c->cap_retry),  need_faces || c->cap_faces};
         hipDeviceSynchronize();
         free_all(c);
-        const int64_t NT = n_total, NO = n_owned;
-        TRY(dalloc(&c->items, n_items));
-        TRY(hipHostMalloc((void **)&c->h_items, sizeof(DevItem) * (size_t)n_items, hipHostMallocDefault));
-        TRY(hipHostMalloc((void **)&c->h_counters, sizeof(uint32_t) * CTR_COUNT, hipHostMallocDefault));
-        for (int k = 0; k < 2; ++k) {
-            TRY(dalloc(&c->keys[k], NT + 1));
-            TRY(dalloc(&c->vals[k], NT + 1));
+        hipError_t e = alloc_all(c, grown);
+        if (e == hipErrorOutOfMemory) {
+            (void)hipGetLastError();
+            e = alloc_all(c, need);
         }
-        TRY(dalloc(&c->hist, hist_need));
-        TRY(dalloc(&c->scan_tmp, scan_need));
-        TRY(hipMalloc(&c->spos, sizeof(double4) * (size_t)NT));
-        TRY(dalloc(&c->sgid, NT));
-        TRY(dalloc(&c->srow, NT));
-        TRY(dalloc(&c->sorig, NT));
-        TRY(dalloc(&c->tab, tab_total));
-        TRY(dalloc(&c->cells, NO));
-        TRY(dalloc(&c->row2cell, NO));
-        TRY(dalloc(&c->cvol, NO));
-        TRY(dalloc(&c->crad, NO));
-        TRY(dalloc(&c->ccnt, NO));
-        TRY(dalloc(&c->crow, NO));
-        TRY(dalloc(&c->cstat, NO));
-        TRY(dalloc(&c->cnv, NO));
-        TRY(dalloc(&c->cnp, NO));
-        TRY(dalloc(&c->cnt, NO));
-        TRY(dalloc(&c->ctopo, NO * VT_TOPO_STRIDE));
-        TRY(dalloc(&c->cnf, NO));
-        const int64_t slots = NO * VT_FSTRIDE_FAST + retry_need * VT_FSTRIDE_BIG;
-        TRY(dalloc(&c->stage_ids, slots));
-        if (need_faces) {
-            TRY(dalloc(&c->stage_area, slots));
-            TRY(dalloc(&c->stage_cen, 3 * slots));
-        }
-        TRY(dalloc(&c->queue, retry_need));
-        TRY(dalloc(&c->gqueue, retry_need));
-        TRY(dalloc(&c->counters, CTR_COUNT));
-        TRY(dalloc(&c->rowoff, NO + 1));
-        c->cap_total = NT;
-        c->cap_owned = NO;
-        c->cap_tab = tab_total;
-        c->cap_items = n_items;
-        c->cap_hist = hist_need;
-        c->cap_scan = scan_need;
-        c->cap_retry = retry_need;
-        c->cap_faces = need_faces;
+        TRY(e);
     }
     memcpy(c->h_items, di.data(), sizeof(DevItem) * (size_t)n_items);
     clear_stale_error();

@@ -75,13 +75,15 @@ struct vt_ctx {
     bool faces_valid = false;
     bool built = false;
 
-    // capacities of the allocations below
+    // the build's scratch: one device and one pinned allocation, divided among the pointers below
+    void *slab = nullptr, *h_slab = nullptr;
+    // capacities of its parts
     int64_t cap_total = 0, cap_owned = 0, cap_tab = 0, cap_retry = 0, cap_items = 0, cap_hist = 0;
     int64_t cap_scan = 0;
     bool cap_faces = false;
 
     DevItem *items = nullptr;      // device copy
-    DevItem *h_items = nullptr;    // host copy (pinned not needed)
+    DevItem *h_items = nullptr;    // host copy
     // sort
     uint64_t *keys[2] = {nullptr, nullptr};
     uint32_t *vals[2] = {nullptr, nullptr};
