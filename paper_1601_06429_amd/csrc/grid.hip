@@ -940,7 +940,7 @@ __device__ __forceinline__ void morton_range(const SampleArgs &A, const DevItem 
     }
 }
 
-// One point's nearest particle by its own search (used where a tile's region is dense): from the
+// One point's nearest particle by its own search (for points no cell claims): from the
 // point's Morton cell (coarsened while empty, refined while it holds more than 32 particles),
 // shells of cells at growing Chebyshev distance k until the best distance is below the point's
 // distance to the sides of the (2k+1)^3 block less two key quanta.
