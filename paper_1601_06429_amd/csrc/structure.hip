@@ -535,12 +535,12 @@ void vt_struct_free(vt_ctx *c) {
     c->st_slow = nullptr;
     c->smark = nullptr;
     c->squeue = nullptr;
-    c->cap_struct = 0;
+    c->cap_struct = c->cap_squeue = 0;
 }
 
 static hipError_t reserve_structure(vt_ctx *c) {
     const int64_t n = c->n_owned;
-    if (c->cap_struct >= n && c->st_cnt) return hipSuccess;
+    if (c->cap_struct >= n && c->cap_squeue >= c->cap_retry && c->st_cnt) return hipSuccess;
     vt_struct_free(c);
     hipError_t e = hipMalloc(&c->st_cnt, sizeof(int64_t) * 3 * (size_t)n);
     if (e == hipSuccess) e = hipMalloc(&c->st_lbase, sizeof(int64_t) * (size_t)(n + 1));
@@ -548,8 +548,12 @@ static hipError_t reserve_structure(vt_ctx *c) {
     if (e == hipSuccess) e = hipMalloc(&c->st_slow, sizeof(int32_t) * (size_t)n);
     if (e == hipSuccess) e = hipMalloc(&c->smark, (size_t)n);
     if (e == hipSuccess) e = hipMalloc(&c->squeue, sizeof(int32_t) * (size_t)c->cap_retry);
-    if (e == hipSuccess) c->cap_struct = n;
-    else vt_struct_free(c);
+    if (e == hipSuccess) {
+        c->cap_struct = n;
+        c->cap_squeue = c->cap_retry;
+    } else {
+        vt_struct_free(c);
+    }
     return e;
 }
 

@@ -167,7 +167,7 @@ struct vt_ctx {
     int32_t *st_slow = nullptr;
     uint8_t *smark = nullptr;
     int32_t *squeue = nullptr;
-    int64_t cap_struct = 0;
+    int64_t cap_struct = 0, cap_squeue = 0;
     // grid tensors (spectral.hip): planes of Nyquist values (complex)
     void *spec_buf = nullptr;
     int64_t cap_spec = 0;
