@@ -8,10 +8,12 @@
 // binary search inside a level-T cell gives them for l > T.  This replaces the
 // search structure the paper gets from Qhull (section 2) with one whose memory
 // accesses are contiguous ranges.
+#include <algorithm>
+
 #include "vt_internal.h"
 
-#define SORT_THREADS 256
-#define SORT_ITEMS 16
+#define SORT_THREADS 512
+#define SORT_ITEMS 8
 #define SORT_TILE (SORT_THREADS * SORT_ITEMS)
 
 // ------------------------------------------------------------------ scan
@@ -190,26 +192,37 @@ __device__ __forceinline__ int find_item(const DevItem *items, int n_items, int6
 }
 
 template <typename PT>
-__global__ void k_keys(const PT *pos, int64_t n, const DevItem *items, int n_items, uint64_t *keys, uint32_t *vals) {
-    int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= n) return;
-    int b = find_item(items, n_items, p);
-    const DevItem &it = items[b];
+__device__ __forceinline__ uint64_t particle_key(const PT *pos, int64_t p, const DevItem &it, int b) {
     uint64_t q[3];
     for (int a = 0; a < 3; ++a) {
         double x = (double)pos[3 * p + a];
         if (it.periodic) x -= it.L[a] * floor((x - it.lo[a]) / it.L[a]);
         q[a] = (uint64_t)vt_qclamp(vt_qraw(x, it.lo[a], it.inv_res));
     }
-    keys[p] = ((uint64_t)b << VT_LOCAL_KEY_BITS) | vt_morton(q[0], q[1], q[2]);
-    vals[p] = (uint32_t)p;
+    return ((uint64_t)b << VT_LOCAL_KEY_BITS) | vt_morton(q[0], q[1], q[2]);
+}
+
+// (also clears the build's counters, the first kernel of a build: a launch less); vals: the particle
+// itself, or for k_sort_count whether it is owned
+template <typename PT>
+__global__ void k_keys(const PT *pos, int64_t n, const DevItem *items, int n_items, uint64_t *keys, uint32_t *vals,
+                       bool owned, uint32_t *counters) {
+    int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (p < CTR_COUNT) counters[p] = 0u;
+    if (p >= n) return;
+    const int b = find_item(items, n_items, p);
+    const DevItem &it = items[b];
+    keys[p] = particle_key(pos, p, it, b);
+    vals[p] = owned ? (uint32_t)(p - it.start < it.n_owned) : (uint32_t)p;
 }
 
 // ------------------------------------------------------------------ radix sort
+// A tile's counts go to hist[digit * sd + block * sb]: by digit where the counts are scanned as one
+// array, by block where the scatter sums them itself.
 __global__ void __launch_bounds__(SORT_THREADS) k_radix_hist(const uint64_t *keys, int64_t n, int shift,
-                                                             int32_t *hist, int nblocks) {
+                                                             int32_t *hist, int64_t sd, int64_t sb) {
     __shared__ int32_t h[256];
-    h[threadIdx.x] = 0;
+    if (threadIdx.x < 256) h[threadIdx.x] = 0;
     __syncthreads();
     int64_t base = (int64_t)blockIdx.x * SORT_TILE;
     for (int i = 0; i < SORT_ITEMS; ++i) {
@@ -217,121 +230,147 @@ __global__ void __launch_bounds__(SORT_THREADS) k_radix_hist(const uint64_t *key
         if (k < n) atomicAdd(&h[(keys[k] >> shift) & 255u], 1);
     }
     __syncthreads();
-    hist[(int64_t)threadIdx.x * nblocks + blockIdx.x] = h[threadIdx.x];
+    if (threadIdx.x < 256) hist[threadIdx.x * sd + blockIdx.x * sb] = h[threadIdx.x];
 }
 
-// Stable scatter of one tile.  Keys are ranked in index order: round-major, then wave, then lane;
-// lanes holding the same digit are found with eight ballots.  The tile is first reordered by digit
-// in LDS (its digit counts are the histogram's, their prefix the digits' starts in the tile), then
-// written out in that order: consecutive threads write consecutive slots of each digit's run (16
-// keys per digit on average), not one scattered slot each.  Thread t brings digit t's count in the
-// tile and its global offset.
-__device__ __forceinline__ void radix_scatter_tile(const uint64_t *kin, const uint32_t *vin, uint64_t *kout,
-                                                   uint32_t *vout, int64_t n, int shift, int64_t base,
-                                                   int32_t count_t, int64_t offset_t) {
-    __shared__ int32_t running[256];   // next slot of each digit in the reordered tile
-    __shared__ int64_t gbase[256];     // the digit's global offset minus its start in the tile
-    __shared__ int32_t wcnt[SORT_THREADS / 64][256];
-    __shared__ int32_t scan_lds[SORT_THREADS];
-    __shared__ uint64_t lkey[SORT_TILE];
-    __shared__ uint32_t lval[SORT_TILE];
-    const int t = threadIdx.x, w = t >> 6, lane = t & 63;
-    {
-        int32_t tot;
-        const int32_t start = block_exclusive_scan<int32_t>(count_t, scan_lds, &tot);
-        running[t] = start;
-        gbase[t] = offset_t - start;
+// exclusive scan of one value per thread of the first 256 (the others' v is ignored); lds: 4 ints.
+// Two barriers; every thread of the block calls it.
+__device__ __forceinline__ int32_t digit_scan(int32_t v, int32_t *lds) {
+    const int t = threadIdx.x, lane = t & 63;
+    int32_t incl = v;
+    for (int o = 1; o < 64; o <<= 1) {
+        const int32_t y = __shfl_up(incl, o);
+        if (lane >= o) incl += y;
     }
+    if (t < 256 && lane == 63) lds[t >> 6] = incl;
+    __syncthreads();
+    int32_t pre = incl - v;
+    for (int ww = 0; ww < 3; ++ww)
+        if ((t >> 6) > ww) pre += lds[ww];
+    __syncthreads();
+    return pre;
+}
+
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Stable ranks of a tile's keys by one digit.  A wavefront holds 64 x IT consecutive keys (round i,
+// lane l: its key 64 i + l) and counts its digits by itself, in its own row of wcnt: the lanes with
+// the same digit are found with eight ballots and the first of them moves the counter, so the rounds
+// need no barrier (a counter shared by the block's wavefronts took four a round, and the scatter 21 us
+// a pass at 64 tiles).  One prefix over the wavefronts and one over the digits then give each key its
+// slot in the tile ordered by digit.  dstart: the digits' starts in the tile; returns, in thread t <
+// 256, the tile's count of digit t.
+template <int NW, int IT>
+__device__ __forceinline__ int32_t tile_rank(const uint64_t (&key)[IT], int cnt, int shift, uint16_t (*wcnt)[256],
+                                             int32_t *lds, int32_t *dstart, int (&slot)[IT]) {
+    const int t = threadIdx.x, w = t >> 6, lane = t & 63;
     const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    for (int i = 0; i < SORT_ITEMS; ++i) {
-        for (int ww = 0; ww < SORT_THREADS / 64; ++ww) wcnt[ww][t] = 0;
-        __syncthreads();
-        int64_t k = base + (int64_t)i * SORT_THREADS + t;
-        bool valid = k < n;
-        uint64_t key = valid ? kin[k] : 0ull;
-        uint32_t val = valid ? vin[k] : 0u;
-        uint32_t d = (uint32_t)(key >> shift) & 255u;
+    for (int k = 0; k < 4; ++k) wcnt[w][64 * k + lane] = 0;
+    wave_lds_order();
+    for (int i = 0; i < IT; ++i) {
+        const bool valid = (w * IT + i) * 64 + lane < cnt;
+        const uint32_t d = (uint32_t)(key[i] >> shift) & 255u;
         uint64_t match = __ballot(valid);
         for (int bit = 0; bit < 8; ++bit) {
-            uint64_t b = __ballot(valid && ((d >> bit) & 1u));
+            const uint64_t b = __ballot((d >> bit) & 1u);
             match &= ((d >> bit) & 1u) ? b : ~b;
         }
-        int rank = __popcll(match & lt);
-        if (valid && rank == 0) wcnt[w][d] = __popcll(match);
-        __syncthreads();
-        int pre = 0;
-        for (int ww = 0; ww < w; ++ww) pre += wcnt[ww][d];
-        if (valid) {
-            const int slot = running[d] + pre + rank;
-            lkey[slot] = key;
-            lval[slot] = val;
-        }
-        __syncthreads();
-        int add = 0;
-        for (int ww = 0; ww < SORT_THREADS / 64; ++ww) add += wcnt[ww][t];
-        running[t] += add;
-        __syncthreads();
+        const int rank = __popcll(match & lt);
+        const int before = wcnt[w][d];
+        wave_lds_order();
+        if (valid && rank == 0) wcnt[w][d] = (uint16_t)(before + __popcll(match));
+        wave_lds_order();
+        slot[i] = before + rank;
     }
-    const int64_t left = n - base;
+    __syncthreads();
+    int32_t tot = 0;
+    if (t < 256)
+        for (int ww = 0; ww < NW; ++ww) {
+            const int32_t c = wcnt[ww][t];
+            wcnt[ww][t] = (uint16_t)tot;
+            tot += c;
+        }
+    const int32_t start = digit_scan(tot, lds);
+    if (t < 256) dstart[t] = start;
+    __syncthreads();
+    for (int i = 0; i < IT; ++i) {
+        const uint32_t d = (uint32_t)(key[i] >> shift) & 255u;
+        slot[i] += wcnt[w][d] + dstart[d];
+    }
+    return tot;
+}
+
+// One pass's scatter of a tile: reordered by digit in LDS, then written out in that order, so that
+// consecutive threads write consecutive slots of each digit's run (16 keys per digit on average).
+// offs null: the block sums the counts of the tiles before its own itself (hist by block), both halves
+// of it every other tile; else offs holds the scan of all counts (hist by digit).
+__global__ void __launch_bounds__(SORT_THREADS) k_radix_scatter(const uint64_t *kin, const uint32_t *vin,
+                                                                uint64_t *kout, uint32_t *vout, int64_t n,
+                                                                int shift, const int32_t *hist, const int32_t *offs,
+                                                                int nblocks) {
+    constexpr int NW = SORT_THREADS / 64;
+    __shared__ uint16_t wcnt[NW][256];
+    __shared__ int32_t scan_lds[4], dstart[256], gbase[256], part[2][2][256];
+    __shared__ uint64_t lkey[SORT_TILE];
+    __shared__ uint32_t lval[SORT_TILE];
+    const int t = threadIdx.x, w = t >> 6, lane = t & 63, blk = (int)blockIdx.x;
+    const int64_t base = (int64_t)blk * SORT_TILE, left = n - base;
     const int cnt = left < (int64_t)SORT_TILE ? (int)left : SORT_TILE;
+    uint64_t key[SORT_ITEMS];
+    uint32_t val[SORT_ITEMS];
+    for (int i = 0; i < SORT_ITEMS; ++i) {
+        const int k = (w * SORT_ITEMS + i) * 64 + lane;
+        key[i] = k < cnt ? kin[base + k] : 0ull;
+        val[i] = k < cnt ? vin[base + k] : 0u;
+    }
+    int32_t off = 0;
+    if (offs) {
+        if (t < 256) off = offs[(int64_t)t * nblocks + blk];
+    } else {
+        const int d = t & 255, h = t >> 8;
+        int32_t before = 0, all = 0;
+#pragma unroll 16
+        for (int b = h; b < nblocks; b += SORT_THREADS / 256) {
+            const int32_t c = hist[(int64_t)b * 256 + d];
+            all += c;
+            before += b < blk ? c : 0;
+        }
+        part[0][h][d] = before;
+        part[1][h][d] = all;
+        __syncthreads();
+        int32_t tot = 0;
+        if (t < 256) {
+            off = part[0][0][t] + part[0][1][t];
+            tot = part[1][0][t] + part[1][1][t];
+        }
+        off += digit_scan(tot, scan_lds);
+    }
+    int slot[SORT_ITEMS];
+    tile_rank<NW, SORT_ITEMS>(key, cnt, shift, wcnt, scan_lds, dstart, slot);
+    if (t < 256) gbase[t] = off - dstart[t];
+    for (int i = 0; i < SORT_ITEMS; ++i)
+        if ((w * SORT_ITEMS + i) * 64 + lane < cnt) {
+            lkey[slot[i]] = key[i];
+            lval[slot[i]] = val[i];
+        }
+    __syncthreads();
     for (int idx = t; idx < cnt; idx += SORT_THREADS) {
-        const uint64_t key = lkey[idx];
-        const int64_t pos = gbase[(uint32_t)(key >> shift) & 255u] + idx;
-        kout[pos] = key;
+        const uint64_t k = lkey[idx];
+        const int32_t pos = gbase[(uint32_t)(k >> shift) & 255u] + idx;
+        kout[pos] = k;
         vout[pos] = lval[idx];
     }
 }
 
-__global__ void __launch_bounds__(SORT_THREADS) k_radix_scatter(const uint64_t *kin, const uint32_t *vin,
-                                                                uint64_t *kout, uint32_t *vout, int64_t n,
-                                                                int shift, const int32_t *counts,
-                                                                const int32_t *offs, int nblocks) {
-    const int t = threadIdx.x;
-    radix_scatter_tile(kin, vin, kout, vout, n, shift, (int64_t)blockIdx.x * SORT_TILE,
-                       counts[(int64_t)t * nblocks + blockIdx.x], (int64_t)offs[(int64_t)t * nblocks + blockIdx.x]);
-}
-
-// The whole sort of at most one tile (SORT_TILE keys) in one block: every pass's histogram, digit
-// offsets and scatter, the passes ping-ponging between the two buffers (a pass reads what the
-// block wrote in the one before, after a block barrier).  Small inputs then take one launch
-// instead of five per pass.
-__global__ void __launch_bounds__(SORT_THREADS) k_radix_tile(uint64_t *k0, uint32_t *v0, uint64_t *k1, uint32_t *v1,
-                                                             int64_t n, int key_bits) {
-    __shared__ int32_t h[256];
-    __shared__ int32_t scan_h[SORT_THREADS];
-    const int t = threadIdx.x;
-    uint64_t *kin = k0, *kout = k1;
-    uint32_t *vin = v0, *vout = v1;
-    for (int shift = 0; shift < key_bits; shift += 8) {
-        h[t] = 0;
-        __syncthreads();
-        for (int i = 0; i < SORT_ITEMS; ++i) {
-            const int64_t k = (int64_t)i * SORT_THREADS + t;
-            if (k < n) atomicAdd(&h[(kin[k] >> shift) & 255u], 1);
-        }
-        __syncthreads();
-        const int32_t cnt = h[t];
-        int32_t tot;
-        const int32_t off = block_exclusive_scan<int32_t>(cnt, scan_h, &tot);
-        radix_scatter_tile(kin, vin, kout, vout, n, shift, 0, cnt, (int64_t)off);
-        __syncthreads();
-        uint64_t *tk = kin;
-        kin = kout;
-        kout = tk;
-        uint32_t *tv = vin;
-        vin = vout;
-        vout = tv;
-    }
-}
-
 // ------------------------------------------------------------------ sorted arrays
+// particle p as the j-th of the sorted arrays; returns its row (-1: not owned)
 template <typename PT, typename PT4>
-__global__ void k_sorted_gather(const PT *pos, const int32_t *gid, const uint32_t *order, int64_t n,
-                                const DevItem *items, int n_items, PT4 *spos, int32_t *sgid, int32_t *srow,
-                                int32_t *sorig) {
-    int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= n) return;
-    int64_t p = order[j];
+__device__ __forceinline__ int32_t put_sorted(const PT *pos, const int32_t *gid, int64_t p, int64_t j,
+                                              const DevItem *items, int n_items, PT4 *spos, int32_t *sgid,
+                                              int32_t *srow, int32_t *sorig) {
     int b = find_item(items, n_items, p);
     const DevItem &it = items[b];
     PT4 v;
@@ -350,8 +389,88 @@ __global__ void k_sorted_gather(const PT *pos, const int32_t *gid, const uint32_
     spos[j] = v;
     sgid[j] = gid ? gid[p] : (int32_t)p;
     int64_t k = p - it.start;
-    srow[j] = (k < it.n_owned) ? (int32_t)(it.owned_base + k) : -1;
+    const int32_t r = (k < it.n_owned) ? (int32_t)(it.owned_base + k) : -1;
+    srow[j] = r;
     sorig[j] = (int32_t)p;
+    return r;
+}
+
+// all_owned: no particle is a buffer one, so the owned cells in Morton order are the sorted particles
+// and the list is written here (five launches less than flags, scan and compaction)
+template <typename PT, typename PT4>
+__global__ void k_sorted_gather(const PT *pos, const int32_t *gid, const uint32_t *order, int64_t n,
+                                const DevItem *items, int n_items, PT4 *spos, int32_t *sgid, int32_t *srow,
+                                int32_t *sorig, bool all_owned, int32_t *cells, int32_t *row2cell) {
+    int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (j >= n) return;
+    const int32_t r = put_sorted(pos, gid, (int64_t)order[j], j, items, n_items, spos, sgid, srow, sorig);
+    if (all_owned) {
+        cells[j] = (int32_t)j;
+        row2cell[r] = (int32_t)j;
+    }
+}
+
+// Small inputs: every particle's place is the number of keys before its own (equal ones by input
+// order), counted by comparing all pairs.  That is n^2 / 64 wavefront compares, but one launch that
+// fills the chip, against two latency-bound ones for each of six radix passes.  A block places
+// COUNT_KEYS keys, each wavefront counting a quarter of the input: its compares' masks are counted by
+// the scalar unit, and those of owned particles give the place in the list of owned cells.  It then
+// writes its particles' sorted arrays itself.  4096 particles: 11 us (a radix sort by one block, 111 us,
+// or 45 with the keys kept in LDS over the passes and the gather and the list of owned cells in it).
+#define COUNT_KEYS 16  // a divisor of 64: a block's keys lie in one chunk of 64
+template <typename PT, typename PT4, bool ALL_OWNED>
+__global__ void __launch_bounds__(256) k_sort_count(const PT *pos, const int32_t *gid, const uint64_t *keys,
+                                                    const uint32_t *owned, int n, const DevItem *items,
+                                                    int n_items, uint64_t *skey, PT4 *spos, int32_t *sgid,
+                                                    int32_t *srow, int32_t *sorig, int32_t *cells,
+                                                    int32_t *row2cell) {
+    __shared__ int32_t part[2][4][COUNT_KEYS];
+    const int t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
+    const int j0 = (int)blockIdx.x * COUNT_KEYS, chunk = j0 & ~63;
+    uint64_t K[COUNT_KEYS];
+    for (int q = 0; q < COUNT_KEYS; ++q) K[q] = keys[min(j0 + q, n - 1)];
+    int32_t before[COUNT_KEYS], own[COUNT_KEYS];
+    for (int q = 0; q < COUNT_KEYS; ++q) before[q] = own[q] = 0;
+    auto count = [&](int base, auto below) {
+        const int k = base + lane;
+        const uint64_t key = k < n ? keys[k] : ~0ull;  // a key has at most 63 bits here: no padding is below one
+        uint64_t mine = 0;
+        if (!ALL_OWNED) {
+            const uint32_t o = k < n ? owned[k] : 0u;
+            mine = __ballot(o != 0);
+        }
+#pragma unroll
+        for (int q = 0; q < COUNT_KEYS; ++q) {
+            const uint64_t m = __ballot(below(key, k, q));
+            before[q] += __popcll(m);
+            if (!ALL_OWNED) own[q] += __popcll(m & mine);
+        }
+    };
+    // the chunks before the block's own (an equal key goes first there), its own, those after
+    int base = 64 * w;
+#pragma unroll 2
+    for (; base < chunk; base += 256) count(base, [&](uint64_t key, int, int q) { return key <= K[q]; });
+    if (base == chunk) {
+        count(base, [&](uint64_t key, int k, int q) { return key < K[q] || (key == K[q] && k < j0 + q); });
+        base += 256;
+    }
+#pragma unroll 2
+    for (; base < n; base += 256) count(base, [&](uint64_t key, int, int q) { return key < K[q]; });
+    for (int q = 0; q < COUNT_KEYS; ++q)
+        if (lane == q) {
+            part[0][w][q] = before[q];
+            part[1][w][q] = own[q];
+        }
+    __syncthreads();
+    if (t >= COUNT_KEYS || j0 + t >= n) return;
+    const int j = part[0][0][t] + part[0][1][t] + part[0][2][t] + part[0][3][t];
+    const int c = ALL_OWNED ? j : part[1][0][t] + part[1][1][t] + part[1][2][t] + part[1][3][t];
+    skey[j] = keys[j0 + t];
+    const int32_t r = put_sorted(pos, gid, (int64_t)(j0 + t), (int64_t)j, items, n_items, spos, sgid, srow, sorig);
+    if (r >= 0) {
+        cells[c] = j;
+        row2cell[r] = c;
+    }
 }
 
 // level-T table: tab[off + c] = first sorted index whose level-T cell is >= c.  The entries from
@@ -504,49 +623,71 @@ __global__ void k_owned_compact(const int32_t *srow, const int32_t *scan, int64_
     }
 }
 
-hipError_t vt_launch_sort(vt_ctx *c, const void *pos, const int32_t *gid) {
+// Up to this many tiles the blocks of the scatter sum the tiles' counts themselves, each reading all of
+// them (1 KB a tile); beyond, the counts are scanned, in three launches more a pass.  Whole builds,
+// summed | scanned: 300000 particles (74 tiles) 3742 | 3809 us, 600000 (147) 6946 | 7002, 1000000 (245)
+// 11468 | 11520.
+#define SORT_DIRECT_TILES 256
+// Up to this many particles a build sorts by comparing all pairs.  Whole builds of uniform particles,
+// compared | by radix passes: 4096 195 | 248 us, 16384 368 | 415, 24000 477 | 497, 32768 615 | 592;
+// with a third of them buffer particles 16384 320 | 361, 24000 426 | 411.
+#define SORT_COUNT_MAX 20480
+
+template <typename PT, typename PT4>
+static hipError_t launch_sort(vt_ctx *c, const PT *pos, const int32_t *gid) {
     hipStream_t s = c->stream;
     const int64_t n = c->n_total;
     const int nb = (int)((n + SORT_TILE - 1) / SORT_TILE);
     const int tpb = 256;
     const int64_t grid = (n + tpb - 1) / tpb;
-    if (c->dtype == VT_F32)
-        k_keys<float><<<grid, tpb, 0, s>>>((const float *)pos, n, c->items, c->n_items, c->keys[0], c->vals[0]);
-    else
-        k_keys<double><<<grid, tpb, 0, s>>>((const double *)pos, n, c->items, c->n_items, c->keys[0], c->vals[0]);
+    const bool all_owned = c->n_owned == n;
+    if (nb > SCAN_THREADS * 64) return hipErrorInvalidValue;  // the scans' limit
+    const bool count = n <= SORT_COUNT_MAX;
+    k_keys<PT><<<(std::max<int64_t>(n, CTR_COUNT) + tpb - 1) / tpb, tpb, 0, s>>>(pos, n, c->items, c->n_items, c->keys[0],
+                                                                               c->vals[0], count, c->counters);
     int cur = 0;
-    if (nb == 1) {
-        // one tile: the whole radix sort in one block
-        k_radix_tile<<<1, SORT_THREADS, 0, s>>>(c->keys[0], c->vals[0], c->keys[1], c->vals[1], n, c->key_bits);
-        cur = ((c->key_bits + 7) / 8) & 1;
-    }
-    for (int shift = 0; nb > 1 && shift < c->key_bits; shift += 8) {
-        k_radix_hist<<<nb, SORT_THREADS, 0, s>>>(c->keys[cur], n, shift, c->hist, nb);
-        hipError_t e = vt_launch_scan_i32(c->hist, c->hist + (int64_t)256 * nb, (int64_t)256 * nb, c->scan_tmp, s);
-        if (e != hipSuccess) return e;
-        k_radix_scatter<<<nb, SORT_THREADS, 0, s>>>(c->keys[cur], c->vals[cur], c->keys[cur ^ 1], c->vals[cur ^ 1], n,
-                                                   shift, c->hist, c->hist + (int64_t)256 * nb, nb);
-        cur ^= 1;
+    if (count) {
+        cur = 1;
+        auto *k = all_owned ? k_sort_count<PT, PT4, true> : k_sort_count<PT, PT4, false>;
+        k<<<(n + COUNT_KEYS - 1) / COUNT_KEYS, 256, 0, s>>>(pos, gid, c->keys[0], c->vals[0], (int)n, c->items,
+                                                            c->n_items, c->keys[1],
+                                                            (PT4 *)c->spos, c->sgid, c->srow, c->sorig, c->cells,
+                                                            c->row2cell);
+    } else {
+        const bool direct = nb <= SORT_DIRECT_TILES;
+        int32_t *offs = direct ? nullptr : c->hist + (int64_t)256 * nb;
+        for (int shift = 0; shift < c->key_bits; shift += 8) {
+            k_radix_hist<<<nb, SORT_THREADS, 0, s>>>(c->keys[cur], n, shift, c->hist, direct ? 1 : nb, direct ? 256 : 1);
+            if (!direct) {
+                hipError_t e = vt_launch_scan_i32(c->hist, offs, (int64_t)256 * nb, c->scan_tmp, s);
+                if (e != hipSuccess) return e;
+            }
+            k_radix_scatter<<<nb, SORT_THREADS, 0, s>>>(c->keys[cur], c->vals[cur], c->keys[cur ^ 1], c->vals[cur ^ 1], n,
+                                                       shift, c->hist, offs, nb);
+            cur ^= 1;
+        }
+        k_sorted_gather<PT, PT4><<<grid, tpb, 0, s>>>(pos, gid, c->vals[cur], n, c->items, c->n_items, (PT4 *)c->spos,
+                                                      c->sgid, c->srow, c->sorig, all_owned, c->cells, c->row2cell);
     }
     c->skey = c->keys[cur];
-    if (c->dtype == VT_F32)
-        k_sorted_gather<float, float4><<<grid, tpb, 0, s>>>((const float *)pos, gid, c->vals[cur], n, c->items,
-                                                            c->n_items, (float4 *)c->spos, c->sgid, c->srow, c->sorig);
-    else
-        k_sorted_gather<double, double4><<<grid, tpb, 0, s>>>((const double *)pos, gid, c->vals[cur], n, c->items,
-                                                              c->n_items, (double4 *)c->spos, c->sgid, c->srow,
-                                                              c->sorig);
     // long runs of the table are listed in the spare key buffer (free until the compaction below)
     uint64_t *pieces = c->keys[cur ^ 1];
     const int64_t piece_cap = (n + 1) / 2;
     k_level_table<<<grid, tpb, 0, s>>>(c->skey, n, c->items, c->n_items, c->tab, pieces, piece_cap, c->counters);
     k_level_fill<<<1024, tpb, 0, s>>>(pieces, piece_cap, c->counters, c->tab);
-    // owned cells in Morton order (flags -> scan -> compact); the flag array reuses vals[cur^1]
-    int32_t *flag = (int32_t *)c->vals[cur ^ 1];
-    int32_t *scan = (int32_t *)c->keys[cur ^ 1];
-    k_owned_flags<<<grid, tpb, 0, s>>>(c->srow, n, flag);
-    hipError_t e = vt_launch_scan_i32(flag, scan, n, c->scan_tmp, s);
-    if (e != hipSuccess) return e;
-    k_owned_compact<<<grid, tpb, 0, s>>>(c->srow, scan, n, c->cells, c->row2cell);
+    if (!count && !all_owned) {
+        // owned cells in Morton order (flags -> scan -> compact); the flag array reuses vals[cur^1]
+        int32_t *flag = (int32_t *)c->vals[cur ^ 1];
+        int32_t *scan = (int32_t *)c->keys[cur ^ 1];
+        k_owned_flags<<<grid, tpb, 0, s>>>(c->srow, n, flag);
+        hipError_t e = vt_launch_scan_i32(flag, scan, n, c->scan_tmp, s);
+        if (e != hipSuccess) return e;
+        k_owned_compact<<<grid, tpb, 0, s>>>(c->srow, scan, n, c->cells, c->row2cell);
+    }
     return hipGetLastError();
+}
+
+hipError_t vt_launch_sort(vt_ctx *c, const void *pos, const int32_t *gid) {
+    return c->dtype == VT_F32 ? launch_sort<float, float4>(c, (const float *)pos, gid)
+                              : launch_sort<double, double4>(c, (const double *)pos, gid);
 }

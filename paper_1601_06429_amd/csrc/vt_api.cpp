@@ -257,7 +257,6 @@ vt_status vt_build(vt_ctx **pctx, const void *pos, vt_dtype dtype, const int32_t
     if (c->timed && !c->ev[0])
         for (int k = 0; k < 4; ++k) TRY(hipEventCreate(&c->ev[k]));
     if (c->timed) TRY(hipEventRecord(c->ev[0], c->stream));
-    TRY(vt_launch_zero_u32(c->counters, CTR_COUNT, c->stream));
     TRY(vt_launch_sort(c, pos, global_id));
     if (c->timed) TRY(hipEventRecord(c->ev[1], c->stream));
     TRY(vt_launch_clip(c));
