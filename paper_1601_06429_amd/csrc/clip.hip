@@ -866,7 +866,7 @@ __device__ __forceinline__ void clip_cells(const ClipArgs &A) {
                     // FP64 path: the exact predicate; mixed path: widened by the vertex error bound
                     double marg = 0.0;
                     if (std::is_same<T, float>::value)
-                        marg = nn * (S.u.s.ve[k] + 1e-6 * (sqrt(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]) + 0.5 * nn));
+                        marg = nn * (S.u.s.ve[k] + 0.5e-6 * nn);
                     return sv > -marg;
                 };
 #pragma unroll
@@ -1080,7 +1080,7 @@ __device__ __forceinline__ void clip_cells(const ClipArgs &A) {
                                 // FP64 path: the exact predicate; mixed path: widened by the vertex error bound
                                 double marg = 0.0;
                                 if (std::is_same<T, float>::value)
-                                    marg = nn * ((double)S.P.ste[k] + 1e-6 * (sqrt(vx * vx + vy * vy + vz * vz) + 0.5 * nn));
+                                    marg = nn * ((double)S.P.ste[k] + 0.5e-6 * nn);
                                 return sv > -marg;
                             };
 #pragma unroll

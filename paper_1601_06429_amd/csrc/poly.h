@@ -445,7 +445,9 @@ struct Poly {
 
     T vx[VPL], vy[VPL], vz[VPL];
     uint32_t vt[VPL];
-    float ve[VPL];     // position error bound (mixed)
+    // mixed: bound of the position's error plus 32 ulp of its distance, which every side test adds: with
+    // the distance in it, no test takes a square root per vertex (150k clustered cells: 3.19 -> 2.89 ms)
+    float ve[VPL];
     uint64_t alive[VPL], fa[VPL];
     double R2;         // squared largest vertex distance (conservative)
 
@@ -492,7 +494,7 @@ struct Poly {
             vt[0] = (neg & 1) ? (X | (Z << 8) | (Y << 16)) : (X | (Y << 8) | (Z << 16));
             if constexpr (MIXED) {
                 float r = sqrtf((float)(vx[0] * vx[0] + vy[0] * vy[0] + vz[0] * vz[0]));
-                ve[0] = 4.f * U32 * r;
+                ve[0] = 36.f * U32 * r;
             }
         }
         alive[0] = 0xFFull;
@@ -559,8 +561,7 @@ struct Poly {
             T sv = side<T>(vx[s], vy[s], vz[s], p);
             bool o = sv > T(0);
             if constexpr (MIXED) {
-                float vn = sqrtf(vx[s] * vx[s] + vy[s] * vy[s] + vz[s] * vz[s]);
-                float bound = pnorm * (ve[s] + 32.f * U32 * (ph + vn));
+                float bound = pnorm * (ve[s] + 32.f * U32 * ph);
                 if (al && fabsf(sv) <= bound) {
                     P4<double> qa = S.pl64[vt[s] & 0xFF], qb = S.pl64[(vt[s] >> 8) & 0xFF],
                                qc = S.pl64[(vt[s] >> 16) & 0xFF];
@@ -695,7 +696,7 @@ struct Poly {
                     const float det = intersect3<float>(pa, pb, p, wx, wy, wz);
                     const float kap = S.pln[fa_] * S.pln[fb_] * pnorm / fabsf(det);
                     const float wn = sqrtf(wx * wx + wy * wy + wz * wz);
-                    float err = 16.f * U32 * (kap * (S.plh[fa_] + S.plh[fb_] + ph + wn) + wn);
+                    float err = 16.f * U32 * (kap * (S.plh[fa_] + S.plh[fb_] + ph + wn) + 3.f * wn);
                     if (!(err < 1e30f)) err = 1e30f;
                     ve[s] = err;
                 } else {
