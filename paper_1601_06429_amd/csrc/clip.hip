@@ -765,8 +765,9 @@ __device__ __forceinline__ void clip_cells(const ClipArgs &A) {
         };
 
         // ---- one sweep over the shell [r_lo, r_hi): lanes = particles, planes that cut
-        // no vertex of the current cell are dropped, survivors are applied nearest first
-        auto sweep = [&](double r_lo, double r_hi) {
+        // no vertex of the current cell are dropped, survivors are applied nearest first.
+        // have_ncq, have_total: the shell's pruned cover where the gather has just made it, else -1
+        auto sweep = [&](double r_lo, double r_hi, int have_ncq, int have_total) {
             const double rl2 = r_lo * r_lo, rh2 = r_hi * r_hi;
             int total;
             // stage the cell's vertices for the box pruning of the cover (and the first chunk)
@@ -799,7 +800,11 @@ __device__ __forceinline__ void clip_cells(const ClipArgs &A) {
             int ncq = -1;
             if constexpr (RETRY) ncq = cover_fine(r_hi, r_lo, total);
             const bool fine_ = RETRY && ncq >= 0;
-            if (!fine_) ncq = cover(r_hi, r_lo, total, true);
+            if (!fine_) {
+                ncq = have_ncq;
+                total = have_total;
+                if (ncq < 0) ncq = cover(r_hi, r_lo, total, true);
+            }
             const int32_t *lpre = S.rp, *lrb = S.rb;
             if constexpr (RETRY && VPL > 1) {
                 if (fine_) {
@@ -988,6 +993,8 @@ __device__ __forceinline__ void clip_cells(const ClipArgs &A) {
             // ---- gather particles with r_done <= d < r_next (and a d^2 histogram); the positions
             // of the next 64 are loaded while the current 64 are processed
             int n = direct ? VT_CAND_MAX + 1 : 0;
+            // a cell that has been cut sweeps a shell of more: counting the rest of it took as long again
+            const int nmax = prune ? VT_CAND_MAX : INT_MAX;
             int32_t jn = -1;
             PT4 pn{};
             int rcur = 0;
@@ -998,7 +1005,7 @@ __device__ __forceinline__ void clip_cells(const ClipArgs &A) {
                     pn = ((const PT4 *)A.spos)[jn];
                 }
             }
-            for (int base = 0; base < total; base += WAVE) {
+            for (int base = 0; base < total && n <= nmax; base += WAVE) {
                 const int f = base + lane;
                 bool keep = false;
                 double dx = 0, dy = 0, dz = 0, d2 = 0;
@@ -1053,7 +1060,7 @@ __device__ __forceinline__ void clip_cells(const ClipArgs &A) {
                 continue;
             }
             if (n > VT_CAND_MAX) {
-                sweep(r_done, r_next);
+                sweep(r_done, r_next, prune && !direct ? ncq : -1, total);
             } else {
                 // ---- sort by distance
                 uint32_t k0 = (lane < n) ? S.u.c.ckey[lane] : 0xFFFFFFFFu;
