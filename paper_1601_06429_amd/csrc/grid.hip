@@ -837,9 +837,10 @@ __global__ void __launch_bounds__(256) k_grid(GridArgs A) {
 }
 
 // The normal deposit and, in the first n_large blocks (one wavefront each), the large kernel
-// over the clip's retry queue, so that the few slow cells next to halos overlap the bulk.
+// over the clip's retry queue, so that the few slow cells next to halos overlap the bulk.  Held to two
+// wavefronts per SIMD: at 258 registers, one too few for them, the 2M/256^3 deposit takes 36.8 ms, not 22.3.
 template <typename PT4>
-__global__ void __launch_bounds__(256) k_grid_fused(GridArgs A) {
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k_grid_fused(GridArgs A) {
     extern __shared__ char smem[];
     if ((int)blockIdx.x < A.n_large) {
         if ((threadIdx.x >> 6) != 0) return;
