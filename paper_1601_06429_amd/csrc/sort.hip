@@ -2,12 +2,12 @@
 //
 // Each world (item) is quantised on a 2^16 grid over a cube of side S, and its
 // particles are sorted along the Morton curve (key = item << 48 | morton48) by
-// an LSD radix sort with 8-bit digits.  A Morton cell at level l is then a
-// contiguous range of the sorted arrays; a dense table at level T (8^T cells,
-// about one particle per cell) gives these ranges directly for l <= T, and a
-// binary search inside a level-T cell gives them for l > T.  This replaces the
-// search structure the paper gets from Qhull (section 2) with one whose memory
-// accesses are contiguous ranges.
+// an LSD radix sort with 8-bit digits, or, if few, by comparing all pairs.  A
+// Morton cell at level l is then a contiguous range of the sorted arrays; a
+// dense table at level T (8^T cells, about one particle per cell) gives these
+// ranges directly for l <= T, and a binary search inside a level-T cell gives
+// them for l > T.  This replaces the search structure the paper gets from Qhull
+// (section 2) with one whose memory accesses are contiguous ranges.
 #include <algorithm>
 
 #include "vt_internal.h"
@@ -259,8 +259,8 @@ __device__ __forceinline__ void wave_lds_order() {
 // Stable ranks of a tile's keys by one digit.  A wavefront holds 64 x IT consecutive keys (round i,
 // lane l: its key 64 i + l) and counts its digits by itself, in its own row of wcnt: the lanes with
 // the same digit are found with eight ballots and the first of them moves the counter, so the rounds
-// need no barrier (a counter shared by the block's wavefronts took four a round, and the scatter 21 us
-// a pass at 64 tiles).  One prefix over the wavefronts and one over the digits then give each key its
+// need no barrier (a counter shared by the block's wavefronts took four a round: the scatter 21 us a
+// pass at 64 tiles, now 9).  One prefix over the wavefronts and one over the digits then give each key its
 // slot in the tile ordered by digit.  dstart: the digits' starts in the tile; returns, in thread t <
 // 256, the tile's count of digit t.
 template <int NW, int IT>
@@ -643,16 +643,15 @@ static hipError_t launch_sort(vt_ctx *c, const PT *pos, const int32_t *gid) {
     const bool all_owned = c->n_owned == n;
     if (nb > SCAN_THREADS * 64) return hipErrorInvalidValue;  // the scans' limit
     const bool count = n <= SORT_COUNT_MAX;
-    k_keys<PT><<<(std::max<int64_t>(n, CTR_COUNT) + tpb - 1) / tpb, tpb, 0, s>>>(pos, n, c->items, c->n_items, c->keys[0],
-                                                                               c->vals[0], count, c->counters);
+    k_keys<PT><<<(std::max<int64_t>(n, CTR_COUNT) + tpb - 1) / tpb, tpb, 0, s>>>(
+        pos, n, c->items, c->n_items, c->keys[0], c->vals[0], count, c->counters);
     int cur = 0;
     if (count) {
         cur = 1;
         auto *k = all_owned ? k_sort_count<PT, PT4, true> : k_sort_count<PT, PT4, false>;
         k<<<(n + COUNT_KEYS - 1) / COUNT_KEYS, 256, 0, s>>>(pos, gid, c->keys[0], c->vals[0], (int)n, c->items,
-                                                            c->n_items, c->keys[1],
-                                                            (PT4 *)c->spos, c->sgid, c->srow, c->sorig, c->cells,
-                                                            c->row2cell);
+                                                            c->n_items, c->keys[1], (PT4 *)c->spos, c->sgid, c->srow,
+                                                            c->sorig, c->cells, c->row2cell);
     } else {
         const bool direct = nb <= SORT_DIRECT_TILES;
         int32_t *offs = direct ? nullptr : c->hist + (int64_t)256 * nb;
