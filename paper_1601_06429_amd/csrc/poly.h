@@ -524,7 +524,8 @@ struct Poly {
                 double x = (double)vx[s], y = (double)vy[s], z = (double)vz[s];
                 double d = x * x + y * y + z * z;
                 if constexpr (MIXED) {
-                    double rr = sqrt(d) * (1.0 + 1e-6) + (double)ve[s];
+                    // 1e-6 of the distance beyond the error bound; ve holds 32 ulp of it besides
+                    double rr = sqrt(d) * (1.0 + 1e-6 - 32.0 * (double)U32) + (double)ve[s];
                     d = rr * rr;
                 }
                 r2l = fmax(r2l, d);
