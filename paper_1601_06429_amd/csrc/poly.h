@@ -698,6 +698,24 @@ struct Poly {
                     const float kap = S.pln[fa_] * S.pln[fb_] * pnorm / fabsf(det);
                     const float wn = sqrtf(wx * wx + wy * wy + wz * wz);
                     float err = 16.f * U32 * (kap * (S.plh[fa_] + S.plh[fb_] + ph + wn) + 3.f * wn);
+                    if constexpr (VPL > 1) {
+                        // Near-parallel planes leave FP32 no useful position, and a bound as large as the
+                        // cell puts every covering box and particle in the vertex's reach (one such cell
+                        // took 1.0 ms, the next slowest 0.73): the vertex is then computed in FP64.
+                        if (!(err < 1e-2f * wn)) {
+                            double x, y, z;
+                            const P4<double> qa = S.pl64[fa_], qb = S.pl64[fb_];
+                            const double det64 = intersect3<double>(qa, qb, p64, x, y, z);
+                            const double k64 = (double)S.pln[fa_] * (double)S.pln[fb_] * (double)pnorm / fabs(det64);
+                            const double w64 = sqrt(x * x + y * y + z * z);
+                            const double e64 = 16.0 * 1.2e-16 * (k64 * ((double)(S.plh[fa_] + S.plh[fb_] + ph) + w64) + w64) +
+                                               (2.0 + 32.0) * (double)U32 * w64;
+                            wx = (T)x;
+                            wy = (T)y;
+                            wz = (T)z;
+                            err = (float)(e64 * (1.0 + 1e-6));
+                        }
+                    }
                     if (!(err < 1e30f)) err = 1e30f;
                     ve[s] = err;
                 } else {
