@@ -20,7 +20,10 @@
 //
 // A face lies between two cells and its integrals serve both, with opposite signs: one of the two
 // cells, known to both from their lowest x voxels, takes them with the difference of the weights
-// (value / voxel volume).  The kernel is bound by VALU issue at two wavefronts per SIMD (237 vector
+// (value / voxel volume).  That needs both cells to have the face, as cells rebuilt from their
+// topology records do.  A cell rebuilt from its facet list lacks the faces below its own facet
+// threshold, which need not be small for its neighbour: such a cell integrates all its faces, and its
+// neighbours theirs towards it.  The kernel is bound by VALU issue at two wavefronts per SIMD (237 vector
 // registers, 19 KB of LDS each), so halving the integrals, the face loops and the classification is
 // what counts: 2M cells on 256^3 took 29.5 ms with every face integrated from both sides and take
 // 22.4 ms now (region integrals 9.0, classifying and emitting 5.1, face loops 2.9, choosing the
@@ -36,6 +39,7 @@
 #include "rebuild.h"
 
 #define GRID_BATCH 16  // cells a wavefront takes at a time on large inputs
+#define GRID_ALONE INT32_MIN  // GridArgs.glow: the cell shares no face
 
 template <int VPL>
 struct GridMem {
@@ -78,7 +82,7 @@ struct GridArgs {
     int64_t npos;             // sorted particles (bound of a record's face tags)
     const int32_t *stage_ids;
     const double *gval;       // per sorted particle: its cell's weight value / voxel volume, 0 if it takes no part
-    const int32_t *glow;      // its cell's lowest x voxel
+    const int32_t *glow;      // its cell's lowest x voxel, or GRID_ALONE
     int share;                // faces between two cells are integrated once, for both
     int batch;                // cells a wavefront takes at a time (at most GRID_BATCH)
     uint32_t *counters;
@@ -430,7 +434,8 @@ __device__ __forceinline__ void grid_body(const GridArgs &A, char *smem, int wid
             }
             // full voxels below a face count down to the cell's lowest one, the same for every face of
             // the cell whichever of its two cells integrates it
-            if (A.share) i0[0] = low;
+            const bool share = A.share && low != GRID_ALONE;
+            if (share) i0[0] = low;
             // the cell's voxel box: contributions are summed in LDS when it fits, and each voxel
             // then takes one global atomic
             const int bx = i1[0] - i0[0] + 1, by = i1[1] - i0[1] + 1, bz = i1[2] - i0[2] + 1;
@@ -446,7 +451,7 @@ __device__ __forceinline__ void grid_body(const GridArgs &A, char *smem, int wid
                 nf += __popcll(m);
             }
             wave_sync();
-            // Of the faces shared with a cell that takes part, this cell integrates those where its
+            // Of the faces shared with a cell that takes part and shares, this cell integrates those where its
             // lowest x voxel is the lower one (ties by index; the neighbour decides alike from its
             // side), for both: the integrals are the same with opposite signs, so the voxels take them
             // with the difference of the weights.  A full voxel below the face counts for each of the
@@ -461,9 +466,9 @@ __device__ __forceinline__ void grid_body(const GridArgs &A, char *smem, int wid
                     if (own) {
                         f = S.fid[q];
                         const int32_t tag = S.P.ptag[f];
-                        const double wj = A.share && tag >= 0 ? A.gval[tag] : 0.0;
-                        if (wj != 0.0) {
-                            int lj = A.glow[tag];
+                        const double wj = share && tag >= 0 ? A.gval[tag] : 0.0;
+                        int lj = wj != 0.0 ? A.glow[tag] : GRID_ALONE;
+                        if (lj != GRID_ALONE) {
                             if (it.periodic) {
                                 double jx, jy, jz;
                                 gpos<PT4>(A.spos, tag, jx, jy, jz);
@@ -783,7 +788,8 @@ __device__ __forceinline__ void grid_body(const GridArgs &A, char *smem, int wid
 }
 
 // Before the deposit: each sorted particle's weight (0 for buffer particles, failed cells and zero
-// values) and its cell's lowest x voxel, which the faces of its neighbours read.  A cell inside one
+// values) and its cell's lowest x voxel, which the faces of its neighbours read, or that the cell
+// shares no face because it has no record (the cells of the large clip kernel).  A cell inside one
 // voxel (its ball of radius R, the largest vertex distance, is) deposits its whole volume here and
 // takes no further part.
 template <typename PT4>
@@ -823,6 +829,7 @@ __global__ void __launch_bounds__(256) k_grid_weights(GridArgs A, const int32_t 
                 unsafeAtomicAdd(&A.grid[g], v * A.cvol[c] / hv);
             } else {
                 w = v / hv;
+                if (A.cnf[c] == 0) low = GRID_ALONE;
             }
         }
     }
