@@ -866,14 +866,18 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
 // The tessellation is already built, so each cell claims its points.  Points lie in rows along z, and
 // a row meets the cell in an interval whose ends are linear in the row's (x, y) for each facet plane:
 // a wavefront per cell gives a lane to every row of points within R of the seed (R the cell's largest
-// vertex distance) and takes the facet neighbours' planes one after another, so a row costs a few
-// operations per plane however many points it holds.
+// vertex distance) and takes the planes of the cell's faces one after another, so a row costs a few
+// operations per plane however many points it holds.  The facet list lacks the faces below the facet
+// threshold, and a cell without one of its planes would claim points of its neighbour's: such a cell's
+// faces are taken from its topology record, which lists every one.  A cell without a record whose list
+// is short of a simple polytope's V / 2 + 2 faces leaves its points to the search.
 //
 // Every plane is taken twice, moved inwards and outwards by a margin above all rounding, in this
 // arithmetic and in the reference's: D.y <= |D|^2 / 2 -+ 1e-13 (R + |D|)^2, where the reference's
 // squared distances are off by at most 8 eps (R + |D|)^2 between them, and the ends by 1e-7 of a
 // point spacing more (the points' own coordinates round by eps times the period, up to 2e-11 of a
-// spacing).  Points inside the inner interval are the cell's: stored.  Points between the two are
+// spacing).  Points inside the inner interval are the cell's: stored (unless the build reported an
+// error: coincident particles have the same cell, and the inner interval is taken as empty).  Points between the two are
 // compared with every neighbour by the reference's own squared distances, ties to the smaller id, and
 // claimed through a 64-bit atomic minimum on (global id, sorted index).  A point no cell claims (a
 // failed cell, or an axis with too few points to unwrap) is found by its own exact search.
@@ -881,9 +885,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
 // The kernel is bound by VALU issue (about 15 planes of 8 FP64 operations a round of 64 rows, with
 // the rows of a small cell filling half the lanes) and the latency of a cell's loads.  500k cells on
 // 192^3 points took 3.00 ms with every candidate point tested against the neighbours one by one and
-// take 0.77 ms; 100k cells on 240 x 216 x 192 points (27 a voxel) took 8.4-10.5 ms in tiles of points
-// that shared a list of candidate particles and take 0.53 ms.
-#define VT_CLAIM_NBR 136    // facet neighbours staged per cell (the large clip kernel keeps no more)
+// take 0.76 ms; 100k cells on 240 x 216 x 192 points (27 a voxel) took 8.4-10.5 ms in tiles of points
+// that shared a list of candidate particles and take 0.54 ms.
+#define VT_CLAIM_NBR 136    // faces staged per cell (the large clip kernel keeps no more)
 
 struct SampleArgs {
     const void *spos;
@@ -898,6 +902,10 @@ struct SampleArgs {
     const int64_t *crow;        // facet list: stage_ids[crow .. crow + ccnt)
     const int32_t *ccnt;
     const int32_t *stage_ids;
+    const int32_t *ctopo;       // topology records: face tags first
+    const int32_t *cnf;         // faces in the record (0: no record)
+    const int32_t *cnv;         // vertices of the cell
+    const uint32_t *counters;
     int64_t ncells;
     const double *value;
     double *grid;
@@ -1024,7 +1032,7 @@ __device__ int32_t nearest_particle(const SampleArgs &A, const DevItem &it, cons
 }
 
 struct ClaimPlane {
-    double x, y, z;   // separation D of the facet neighbour
+    double x, y, z;   // separation D of the neighbour across the face
     double c, m;      // |D|^2 / 2 and the margin
     double iz;        // 1 / D_z
 };
@@ -1043,6 +1051,7 @@ __global__ void __launch_bounds__(256) k_sample_claim(SampleArgs A) {
     const int64_t F[3] = {(int64_t)A.nx * sub, (int64_t)A.ny * sub, (int64_t)A.nz * sub};
     const double invL[3] = {uni_d(1.0 / it.L[0]), uni_d(1.0 / it.L[1]), uni_d(1.0 / it.L[2])};
     const double ihf[3] = {uni_d((double)F[0] / it.L[0]), uni_d((double)F[1] / it.L[1]), uni_d((double)F[2] / it.L[2])};
+    const bool clean = A.counters[CTR_STATUS] == 0;
     // each XCD (blocks are dealt to them in turn) takes one contiguous eighth of the Morton order
     const int seg = (int)(blockIdx.x % VT_XCD_SEGMENTS);
     const int64_t c_end = A.ncells * (seg + 1) / VT_XCD_SEGMENTS;
@@ -1054,17 +1063,21 @@ __global__ void __launch_bounds__(256) k_sample_claim(SampleArgs A) {
         const int64_t cl = c0 + lane;
         bool todo = lane < A.batch && cl < c_end;
         if (todo) todo = !(A.cstat[cl] & VT_CELL_FAILED);
-        int32_t j_l = 0, cnt_l = 0;
+        int32_t j_l = 0, cnt_l = 0, rec_l = 0;
         int f0_l[3] = {0, 0, 0}, nf_l[3] = {0, 0, 0};
         double x_l[3] = {0.0, 0.0, 0.0}, R_l = 0.0;
         int64_t row_l = 0;
         if (todo) {
             j_l = A.cells[cl];
-            cnt_l = A.ccnt[cl];
+            const int32_t fc = A.ccnt[cl], nf = A.cnf[cl], nv = A.cnv[cl];
             row_l = A.crow[cl];
+            rec_l = nf != 0 && nf != fc;
+            cnt_l = rec_l ? nf : fc;
+            row_l = rec_l ? cl * VT_TOPO_STRIDE : row_l;
+            todo = nf != 0 || 2 * fc == nv + 4;
             gpos<PT4>(A.spos, j_l, x_l[0], x_l[1], x_l[2]);
             R_l = A.crad[cl] * (1.0 + 1e-9) + 1e-12 * it.S;
-            todo = cnt_l <= VT_CLAIM_NBR && R_l < it.S;  // false for a radius that is not a number
+            todo = todo && cnt_l <= VT_CLAIM_NBR && R_l < it.S;  // false for a radius that is not a number
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
                 const double g = x_l[a] - it.lo[a];
@@ -1094,11 +1107,12 @@ __global__ void __launch_bounds__(256) k_sample_claim(SampleArgs A) {
                 f0[a] = (int)readlane_u32((uint32_t)f0_l[a], i);
                 nf[a] = (int)readlane_u32((uint32_t)nf_l[a], i);
             }
+            const int32_t *list = (readlane_u32((uint32_t)rec_l, i) ? A.ctopo : A.stage_ids) + row;
             const int32_t gi = A.sgid[j0];
             wave_sync();
             for (int k = lane; k < cnt; k += 64) {
                 double px, py, pz;
-                gpos<PT4>(A.spos, A.stage_ids[row + k], px, py, pz);
+                gpos<PT4>(A.spos, max(list[k], 0), px, py, pz);  // no wall (tag below 0) bounds a sound periodic cell
                 double ex = px - x[0], ey = py - x[1], ez = pz - x[2];
                 ex -= it.L[0] * rint(ex * invL[0]);
                 ey -= it.L[1] * rint(ey * invL[1]);
@@ -1144,7 +1158,7 @@ __global__ void __launch_bounds__(256) k_sample_claim(SampleArgs A) {
                 const int a0 = max(f0[2], (int)fmax(ceil((p0 + zb) * ihf[2] - 0.5 - 1e-7), -1e9));
                 const int a1 = min(f0[2] + nf[2] - 1, (int)fmin(floor((p1 + zb) * ihf[2] - 0.5 + 1e-7), 1e9));
                 int b0 = a1 + 1, b1 = a1;   // the points inside for certain
-                if (s1 >= s0) {
+                if (s1 >= s0 && clean) {
                     b0 = min(max(a0, (int)ceil((s0 + zb) * ihf[2] - 0.5 + 1e-7)), a1 + 1);
                     b1 = max(min(a1, (int)floor((s1 + zb) * ihf[2] - 0.5 - 1e-7)), b0 - 1);
                 }
@@ -1163,7 +1177,7 @@ __global__ void __launch_bounds__(256) k_sample_claim(SampleArgs A) {
                     const double d2 = e0 * e0 + e1 * e1 + e2 * e2;
                     bool win = true;
                     for (int k = 0; k < cnt && win; ++k) {
-                        const int32_t j = A.stage_ids[row + k];
+                        const int32_t j = max(list[k], 0);
                         double px, py, pz;
                         gpos<PT4>(A.spos, j, px, py, pz);
                         double ex = px - q0, ey = py - q1, ez = pz - q2;
@@ -1248,6 +1262,10 @@ hipError_t vt_launch_grid_sample(vt_ctx *c, const double *value, int nx, int ny,
     a.crow = c->crow;
     a.ccnt = c->ccnt;
     a.stage_ids = c->stage_ids;
+    a.ctopo = c->ctopo;
+    a.cnf = c->cnf;
+    a.cnv = c->cnv;
+    a.counters = c->counters;
     a.ncells = c->n_owned;
     a.value = value;
     a.grid = grid;
