@@ -1227,8 +1227,20 @@ __device__ __forceinline__ void clip_cells(const ClipArgs &A) {
             if (lane == 0) {
                 C->cnf[cslot] = 0;
                 uint32_t qi = atomicAdd(&C->counters[CTR_QUEUE], 1u);
-                if ((int64_t)qi < C->queue_cap) C->queue_out[qi] = cslot;
-                else atomicOr(&C->counters[CTR_STATUS], VT_DEV_CAPACITY);
+                if ((int64_t)qi < C->queue_cap) {
+                    C->queue_out[qi] = cslot;
+                } else {
+                    // a cell that finds the queue full fails here: its record must not be left as an
+                    // earlier build's, or as nothing at all
+                    atomicOr(&C->counters[CTR_STATUS], VT_DEV_CAPACITY);
+                    C->cvol[cslot] = 0.0;
+                    C->crad[cslot] = 0.0;
+                    C->ccnt[cslot] = 0;
+                    C->crow[cslot] = (int64_t)cslot * C->fstride;
+                    C->cstat[cslot] = VT_CELL_FAILED;
+                    C->cnv[cslot] = 0;
+                    C->cnt[cslot] = ntested;
+                }
                 if (dup) atomicOr(&C->counters[CTR_STATUS], VT_DEV_DUPLICATE);
             }
             continue;

@@ -829,7 +829,9 @@ __global__ void __launch_bounds__(256) k_grid_weights(GridArgs A, const int32_t 
                 unsafeAtomicAdd(&A.grid[g], v * A.cvol[c] / hv);
             } else {
                 w = v / hv;
-                if (A.cnf[c] == 0) low = GRID_ALONE;
+                // (nor does one whose radius is not a length in the box: it must not set the loops' range)
+                const double diag2 = it.L[0] * it.L[0] + it.L[1] * it.L[1] + it.L[2] * it.L[2];
+                if (A.cnf[c] == 0 || !(rc * rc <= diag2 * (1.0 + 1e-9))) low = GRID_ALONE;
             }
         }
     }
