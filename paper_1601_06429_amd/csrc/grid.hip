@@ -364,7 +364,13 @@ __device__ __forceinline__ void grid_body(const GridArgs &A, char *smem, int wid
             tm &= tm - 1ull;
             const int32_t c = (int32_t)readlane_u32((uint32_t)cl, l);
             const int32_t j0 = (int32_t)readlane_u32((uint32_t)jl, l), low = (int32_t)readlane_u32((uint32_t)lowl, l);
-            const double wi = readlane_d(vl, l);
+            // a weight that is not finite is applied to the cell's sums, not to their terms: the terms
+            // outside the cell cancel to zero or next to it, but not once they are infinite
+            const double wl = readlane_d(vl, l), wi = isfinite(wl) ? wl : 1.0;
+            auto scaled = [&](double v) {
+                const double w_ = readlane_d(vl, l);
+                return isfinite(w_) ? v : v * w_;
+            };
             const double sx = readlane_d(xl, l), sy = readlane_d(yl, l), sz = readlane_d(zl, l);
             const double xs[3] = {sx, sy, sz};
             double blo[3], bhi[3];
@@ -661,7 +667,7 @@ __device__ __forceinline__ void grid_body(const GridArgs &A, char *smem, int wid
                     return;
                 }
                 int64_t g = (wrap1(i, dims[0]) * dims[1] + wrap1(j, dims[1])) * dims[2] + wrap1(k, dims[2]);
-                unsafeAtomicAdd(&A.grid[g], v);
+                unsafeAtomicAdd(&A.grid[g], scaled(v));
             };
             // The item's geometry: rectangle corner (seed-relative; integrals are taken relative
             // to it), the face plane n.v = d, and the plane X.  With y, z relative to the corner the
@@ -780,7 +786,7 @@ __device__ __forceinline__ void grid_body(const GridArgs &A, char *smem, int wid
                     const int li = divmod_small(divmod_small(t, bz, lk), by, lj);
                     const int64_t g = (wrap1(i0[0] + li, dims[0]) * dims[1] + wrap1(i0[1] + lj, dims[1])) * dims[2] +
                                       wrap1(i0[2] + lk, dims[2]);
-                    unsafeAtomicAdd(&A.grid[g], v);
+                    unsafeAtomicAdd(&A.grid[g], scaled(v));
                 }
             }
         }
@@ -789,7 +795,8 @@ __device__ __forceinline__ void grid_body(const GridArgs &A, char *smem, int wid
 
 // Before the deposit: each sorted particle's weight (0 for buffer particles, failed cells and zero
 // values) and its cell's lowest x voxel, which the faces of its neighbours read, or that the cell
-// shares no face because it has no record (the cells of the large clip kernel).  A cell inside one
+// shares no face: it has no record (the cells of the large clip kernel), or its weight is not finite and
+// would not cancel against itself in its neighbours' terms.  A cell inside one
 // voxel (its ball of radius R, the largest vertex distance, is) deposits its whole volume here and
 // takes no further part.
 template <typename PT4>
@@ -831,7 +838,7 @@ __global__ void __launch_bounds__(256) k_grid_weights(GridArgs A, const int32_t 
                 w = v / hv;
                 // (nor does one whose radius is not a length in the box: it must not set the loops' range)
                 const double diag2 = it.L[0] * it.L[0] + it.L[1] * it.L[1] + it.L[2] * it.L[2];
-                if (A.cnf[c] == 0 || !(rc * rc <= diag2 * (1.0 + 1e-9))) low = GRID_ALONE;
+                if (A.cnf[c] == 0 || !(rc * rc <= diag2 * (1.0 + 1e-9)) || !isfinite(w)) low = GRID_ALONE;
             }
         }
     }
