@@ -425,7 +425,7 @@ __device__ __forceinline__ void grid_body(const GridArgs &A, char *smem, int wid
                 // it must not drive the loops below
                 const double lo_ = (g0[a] + mn[a] - del[a]) * ih[a], hi_ = (g0[a] + mx[a] - del[a]) * ih[a];
                 sane = sane && isfinite(lo_) && isfinite(hi_) && hi_ >= lo_ && hi_ - lo_ <= (double)dims[a] + 1.0 &&
-                       fabs(lo_) < 1e9 && fabs(hi_) < 1e9;
+                       fabs(lo_) < 2147483646.0 && fabs(hi_) < 2147483646.0;  // and the next index fits in an int
                 i0[a] = uni_i(sane ? (int)floor(lo_) : 0);
                 i1[a] = uni_i(sane ? (int)floor(hi_) : 0);
                 if (!it.periodic) {
