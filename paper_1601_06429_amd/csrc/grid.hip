@@ -882,10 +882,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
 // is short of a simple polytope's V / 2 + 2 faces leaves its points to the search.
 //
 // Every plane is taken twice, moved inwards and outwards by a margin above all rounding, in this
-// arithmetic and in the reference's: D.y <= |D|^2 / 2 -+ 1e-13 (R + |D|)^2, where the reference's
-// squared distances are off by at most 8 eps (R + |D|)^2 between them, and the ends by 1e-7 of a
-// point spacing more (the points' own coordinates round by eps times the period, up to 2e-11 of a
-// spacing).  Points inside the inner interval are the cell's: stored (unless the build reported an
+// arithmetic and in the reference's.  D.y <= |D|^2 / 2 -+ m with m = 1e-13 r^2 + 4e-15 S r, r = R + |D|
+// and S the period: the reference's squared distances round by at most 8 eps r^2 between them, and a
+// separation taken through the wrap by eps S / 2 an axis (of two particles, and here of D and y: less
+// than 1e-15 S r in all).  The ends move by 1e-7 of a point spacing more, and by 1e-15 (|lo| + S),
+// above the rounding of the points' own coordinates wherever the box lies.  Points inside the inner interval are the cell's: stored (unless the build reported an
 // error: coincident particles have the same cell, and the inner interval is taken as empty).  Points between the two are
 // compared with every neighbour by the reference's own squared distances, ties to the smaller id, and
 // claimed through a 64-bit atomic minimum on (global id, sorted index).  A point no cell claims (a
@@ -1061,6 +1062,7 @@ __global__ void __launch_bounds__(256) k_sample_claim(SampleArgs A) {
     const double invL[3] = {uni_d(1.0 / it.L[0]), uni_d(1.0 / it.L[1]), uni_d(1.0 / it.L[2])};
     const double ihf[3] = {uni_d((double)F[0] / it.L[0]), uni_d((double)F[1] / it.L[1]), uni_d((double)F[2] / it.L[2])};
     const bool clean = A.counters[CTR_STATUS] == 0;
+    const double zend = uni_d(1e-7 + 1e-15 * (fabs(it.lo[2]) + it.S) * ihf[2]);
     // each XCD (blocks are dealt to them in turn) takes one contiguous eighth of the Morton order
     const int seg = (int)(blockIdx.x % VT_XCD_SEGMENTS);
     const int64_t c_end = A.ncells * (seg + 1) / VT_XCD_SEGMENTS;
@@ -1127,7 +1129,7 @@ __global__ void __launch_bounds__(256) k_sample_claim(SampleArgs A) {
                 ey -= it.L[1] * rint(ey * invL[1]);
                 ez -= it.L[2] * rint(ez * invL[2]);
                 const double d2 = ex * ex + ey * ey + ez * ez, r = R + sqrt(d2);
-                M.pl[k] = ClaimPlane{ex, ey, ez, 0.5 * d2, 1e-13 * r * r, 1.0 / ez};
+                M.pl[k] = ClaimPlane{ex, ey, ez, 0.5 * d2, 1e-13 * r * r + 4e-15 * it.S * r, 1.0 / ez};
             }
             wave_sync();
             const unsigned long long mine = ((unsigned long long)(uint32_t)gi << 32) | (uint32_t)j0;
@@ -1164,12 +1166,12 @@ __global__ void __launch_bounds__(256) k_sample_claim(SampleArgs A) {
                     }
                 }
                 if (p1 < p0) continue;
-                const int a0 = max(f0[2], (int)fmax(ceil((p0 + zb) * ihf[2] - 0.5 - 1e-7), -1e9));
-                const int a1 = min(f0[2] + nf[2] - 1, (int)fmin(floor((p1 + zb) * ihf[2] - 0.5 + 1e-7), 1e9));
+                const int a0 = max(f0[2], (int)fmax(ceil((p0 + zb) * ihf[2] - 0.5 - zend), -1e9));
+                const int a1 = min(f0[2] + nf[2] - 1, (int)fmin(floor((p1 + zb) * ihf[2] - 0.5 + zend), 1e9));
                 int b0 = a1 + 1, b1 = a1;   // the points inside for certain
                 if (s1 >= s0 && clean) {
-                    b0 = min(max(a0, (int)ceil((s0 + zb) * ihf[2] - 0.5 + 1e-7)), a1 + 1);
-                    b1 = max(min(a1, (int)floor((s1 + zb) * ihf[2] - 0.5 - 1e-7)), b0 - 1);
+                    b0 = min(max(a0, (int)ceil((s0 + zb) * ihf[2] - 0.5 + zend)), a1 + 1);
+                    b1 = max(min(a1, (int)floor((s1 + zb) * ihf[2] - 0.5 - zend)), b0 - 1);
                 }
                 unsigned long long *slot = A.slot + ((int64_t)w0 * F[1] + w1) * F[2];
                 for (int f = a0; f <= a1; ++f) {
