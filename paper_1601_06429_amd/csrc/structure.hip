@@ -17,7 +17,8 @@
 // k_structure_fast from the record alone: no face is dropped, the record's vertex triples are
 // counter-clockwise seen from outside, so a loop needs no area to know its direction, and the faces'
 // order is the rank of their ids.  A cell of the large clip kernel with F = V / 2 + 2 facets (a simple
-// polytope has that many faces) is counted alike.  The others (faces dropped, walls, no record) are
+// polytope has that many faces), none of them small enough to be of rounding's making, is counted
+// alike.  The others (faces dropped, walls, no record) are
 // counted and written by k_structure: rebuilt, their face loops walked lane-parallel for area and
 // direction, one face per lane, and sorted by id with a wave bitonic sort; cells with more than 64
 // vertices by its large variant with four vertex slots per lane.
@@ -314,7 +315,9 @@ __global__ void __launch_bounds__(256) k_structure_count(StructArgs A) {
         if (st & VT_CELL_FAILED) {
             mark = MARK_NONE;
         } else if (st & VT_CELL_RETRIED) {
-            mark = nv >= 4 && 2 * fc == nv + 4 ? MARK_LARGE_COUNTED : MARK_LARGE;
+            // Counted without being rebuilt, a cell that does not close then has room but nothing to
+            // put there.  A facet threshold from 1e-12 on keeps no face that rounding could move.
+            mark = A.area_eps >= 1e-12f && nv >= 4 && 2 * fc == nv + 4 ? MARK_LARGE_COUNTED : MARK_LARGE;
         } else if (nf >= 4 && nf <= VT_TOPO_FACES && nv >= 4 && nv <= 64 && fc == nf) {
             mark = MARK_FAST;
         }
