@@ -12,16 +12,16 @@
 // Two passes over the cells: the first counts (vertices, faces, loop entries) per row, the host
 // scans the counts, and the second writes.
 //
-// Nearly every cell has a topology record whose faces are all in its facet list.  Such a cell is
+// Nearly every cell has a topology record whose faces are all in its facet list.  Such a cell (of a
+// bounded world only if no face is small enough to be of rounding's making: k_structure_count) is
 // counted by one thread (its vertices, its faces, three loop entries per vertex), and written by
 // k_structure_fast from the record alone: no face is dropped, the record's vertex triples are
 // counter-clockwise seen from outside, so a loop needs no area to know its direction, and the faces'
 // order is the rank of their ids.  A cell of the large clip kernel with F = V / 2 + 2 facets (a simple
-// polytope has that many faces), none of them small enough to be of rounding's making, is counted
-// alike.  The others (faces dropped, walls, no record) are
-// counted and written by k_structure: rebuilt, their face loops walked lane-parallel for area and
-// direction, one face per lane, and sorted by id with a wave bitonic sort; cells with more than 64
-// vertices by its large variant with four vertex slots per lane.
+// polytope has that many faces), none of them that small, is counted alike.  The others (faces dropped,
+// walls, no record) are counted and written by k_structure: rebuilt, their face loops walked
+// lane-parallel for area and direction, one face per lane, and sorted by id with a wave bitonic sort;
+// cells with more than 64 vertices by its large variant with four vertex slots per lane.
 //
 // Bound by the latency of dependent loads (cell -> seed -> row -> offsets, tags -> positions) and of
 // LDS.  400k clustered cells: the write pass 2.39 -> 0.42 ms (1.1 TB/s written; 79 vector registers
@@ -312,13 +312,15 @@ __global__ void __launch_bounds__(256) k_structure_count(StructArgs A) {
         const int nf = A.src.cnf[c], nv = A.src.cnv[c], fc = A.src.ccnt[c];
         int64_t v = 0, f = 0;
         uint8_t mark = MARK_SLOW;
+        // Counted without being rebuilt, a cell whose loops do not close has room but nothing to put
+        // there.  A facet threshold from 1e-12 on keeps no face that rounding could make or move.
+        const bool sure = A.area_eps >= 1e-12f;
         if (st & VT_CELL_FAILED) {
             mark = MARK_NONE;
         } else if (st & VT_CELL_RETRIED) {
-            // Counted without being rebuilt, a cell that does not close then has room but nothing to
-            // put there.  A facet threshold from 1e-12 on keeps no face that rounding could move.
-            mark = A.area_eps >= 1e-12f && nv >= 4 && 2 * fc == nv + 4 ? MARK_LARGE_COUNTED : MARK_LARGE;
-        } else if (nf >= 4 && nf <= VT_TOPO_FACES && nv >= 4 && nv <= 64 && fc == nf) {
+            mark = sure && nv >= 4 && 2 * fc == nv + 4 ? MARK_LARGE_COUNTED : MARK_LARGE;
+        } else if (nf >= 4 && nf <= VT_TOPO_FACES && nv >= 4 && nv <= 64 && fc == nf &&
+                   (sure || A.items[item_of(A.items, A.n_items, A.cells[c])].periodic)) {
             mark = MARK_FAST;
         }
         if (mark == MARK_FAST || mark == MARK_LARGE_COUNTED) {

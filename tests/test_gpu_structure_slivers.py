@@ -1,5 +1,5 @@
-"""The structure of a cell of more than 64 vertices some of whose faces are slivers of rounding width:
-neighbours placed so that their planes pass through an edge of the cell (or a gap inside it), with a
+"""The structure of cells of more and fewer than 64 vertices some of whose faces are slivers of rounding width:
+neighbours placed so that their planes pass through an edge of a cell (or a gap inside it), with a
 facet threshold low enough to keep whatever rounding leaves of such faces.  Clipped again in another
 order the cell need not close: it is then left empty and reported.  Otherwise its loops are there and
 use every vertex."""
@@ -48,13 +48,28 @@ def test_slivers(vt, torch_cuda, oracle, seed, gap, eps):
     ctx = vt.Context().vt_build(torch_cuda.from_numpy(p).cuda(), vt.whole_box(n, 0.0, 1.0), want_faces=True, area_eps=eps)
     cells = ctx.vt_cells()
     assert int(cells.status[0]) & 2
+    _check_row(ctx, 0)
+
+
+def _check_row(ctx, i):
     s = ctx.vt_structure()
     code = ctx.vt_query()[0]
     vo, fo, lo = (t.cpu().numpy() for t in (s.vert_off, s.face_off, s.loop_off))
-    if vo[1] == 0:
-        assert code == 8 and fo[1] == 0
+    if vo[i + 1] == vo[i]:
+        assert code == 8 and fo[i + 1] == fo[i]
         return
     lv = s.loop_vert.cpu().numpy()
-    loops = [lv[lo[f]:lo[f + 1]] for f in range(fo[0], fo[1])]
+    loops = [lv[lo[f]:lo[f + 1]] for f in range(fo[i], fo[i + 1])]
     assert min(len(x) for x in loops) >= 3
-    assert np.array_equal(np.unique(np.concatenate(loops)), np.arange(vo[1]))
+    assert np.array_equal(np.unique(np.concatenate(loops)), np.arange(vo[i + 1] - vo[i]))
+
+
+@pytest.mark.parametrize("gap", [0.0, 2e-16, 5e-16])
+@pytest.mark.parametrize("n_shell,n_sliver,seed", [(18, 8, 8), (14, 10, 20), (18, 8, 7), (14, 10, 3)])
+def test_slivers_of_small_cells(vt, torch_cuda, oracle, n_shell, n_sliver, seed, gap):
+    p, k = sliver_world(oracle, seed, n_shell, n_sliver)
+    p[1:1 + k] = p[0] + (p[1:1 + k] - p[0]) * (1.0 - gap)
+    ctx = vt.Context().vt_build(torch_cuda.from_numpy(p).cuda(),
+                                vt.whole_box(len(p), 0.0, 1.0, periodic=False, walls=63), want_faces=True, area_eps=1e-30)
+    assert ctx.vt_query()[0] == 0
+    _check_row(ctx, 0)
