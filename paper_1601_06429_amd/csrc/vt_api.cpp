@@ -237,11 +237,19 @@ vt_status vt_build(vt_ctx **pctx, const void *pos, vt_dtype dtype, const int32_t
     if (realloc_all) {
         // No size shrinks: builds of different shapes on one context in turn (a decomposition's passes:
         // many owned particles, then few with wider buffers) would each find another size too small.
+        // But the facet arrays (1.3 KB a cell) are kept or made only for cells of a build that asks for
+        // them: not grown for a larger build that does not, nor made for as many cells as an earlier one
+        // had.  A caller's own allocations may need the room.
         const BuildSizes need{n_total, n_owned, tab_total, n_items, hist_need, scan_need, retry_need, need_faces};
-        BuildSizes grown{std::max(n_total, c->cap_total),     std::max(n_owned, c->cap_owned),
-                         std::max(tab_total, c->cap_tab),     std::max<int64_t>(n_items, c->cap_items),
-                         std::max(hist_need, c->cap_hist),    std::max(scan_need, c->cap_scan),
-                         std::max(retry_need, c->cap_retry),  need_faces || c->cap_faces};
+        const bool new_faces = need_faces && !c->cap_faces;
+        const BuildSizes grown{std::max(n_total, c->cap_total),
+                               new_faces ? n_owned : std::max(n_owned, c->cap_owned),
+                               std::max(tab_total, c->cap_tab),
+                               std::max<int64_t>(n_items, c->cap_items),
+                               std::max(hist_need, c->cap_hist),
+                               std::max(scan_need, c->cap_scan),
+                               new_faces ? retry_need : std::max(retry_need, c->cap_retry),
+                               need_faces || (c->cap_faces && n_owned <= c->cap_owned)};
         hipDeviceSynchronize();
         free_all(c);
         hipError_t e = alloc_all(c, grown);
