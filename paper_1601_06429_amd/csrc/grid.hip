@@ -366,12 +366,12 @@ __device__ __forceinline__ void grid_body(const GridArgs &A, char *smem, int wid
             const int32_t j0 = (int32_t)readlane_u32((uint32_t)jl, l), low = (int32_t)readlane_u32((uint32_t)lowl, l);
             // a weight that is not finite is applied to the cell's sums, not to their terms: the terms
             // outside the cell cancel to zero or next to it, but not once they are infinite
-            const double wl = readlane_d(vl, l), wi = isfinite(wl) ? wl : 1.0;
+            const double wl = readlane_dbl(vl, l), wi = isfinite(wl) ? wl : 1.0;
             auto scaled = [&](double v) {
-                const double w_ = readlane_d(vl, l);
+                const double w_ = readlane_dbl(vl, l);
                 return isfinite(w_) ? v : v * w_;
             };
-            const double sx = readlane_d(xl, l), sy = readlane_d(yl, l), sz = readlane_d(zl, l);
+            const double sx = readlane_dbl(xl, l), sy = readlane_dbl(yl, l), sz = readlane_dbl(zl, l);
             const double xs[3] = {sx, sy, sz};
             double blo[3], bhi[3];
             for (int a = 0; a < 3; ++a) {
@@ -795,10 +795,9 @@ __device__ __forceinline__ void grid_body(const GridArgs &A, char *smem, int wid
 
 // Before the deposit: each sorted particle's weight (0 for buffer particles, failed cells and zero
 // values) and its cell's lowest x voxel, which the faces of its neighbours read, or that the cell
-// shares no face: it has no record (the cells of the large clip kernel), or its weight is not finite and
-// would not cancel against itself in its neighbours' terms.  A cell inside one
-// voxel (its ball of radius R, the largest vertex distance, is) deposits its whole volume here and
-// takes no further part.
+// shares no face: it has no record (the cells of the large clip kernel), or its weight is not finite
+// and would not cancel against itself in its neighbours' terms.  A cell inside one voxel (its ball of
+// radius R, the largest vertex distance, is) deposits its whole volume here and takes no further part.
 template <typename PT4>
 __global__ void __launch_bounds__(256) k_grid_weights(GridArgs A, const int32_t *srow, const int32_t *row2cell,
                                                       const double *value, double *gval, int32_t *glow) {
@@ -882,15 +881,16 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
 // is short of a simple polytope's V / 2 + 2 faces leaves its points to the search.
 //
 // Every plane is taken twice, moved inwards and outwards by a margin above all rounding, in this
-// arithmetic and in the reference's.  D.y <= |D|^2 / 2 -+ m with m = 1e-13 r^2 + 4e-15 S r, r = R + |D|
-// and S the period: the reference's squared distances round by at most 8 eps r^2 between them, and a
-// separation taken through the wrap by eps S / 2 an axis (of two particles, and here of D and y: less
-// than 1e-15 S r in all).  The ends move by 1e-7 of a point spacing more, and by 1e-15 (|lo| + S),
-// above the rounding of the points' own coordinates wherever the box lies.  Points inside the inner interval are the cell's: stored (unless the build reported an
-// error: coincident particles have the same cell, and the inner interval is taken as empty).  Points between the two are
-// compared with every neighbour by the reference's own squared distances, ties to the smaller id, and
-// claimed through a 64-bit atomic minimum on (global id, sorted index).  A point no cell claims (a
-// failed cell, or an axis with too few points to unwrap) is found by its own exact search.
+// arithmetic and in the reference's.  D.y <= |D|^2 / 2 -+ m with m = 1e-13 r^2 + 4e-15 S r, r = R +
+// |D| and S the period: the reference's squared distances round by at most 8 eps r^2 between them, and
+// a separation taken through the wrap by eps S / 2 an axis (of two particles, and here of D and y:
+// less than 1e-15 S r in all).  The ends move by 1e-7 of a point spacing more, and by 1e-15 (|lo| +
+// S), above the rounding of the points' own coordinates wherever the box lies.  Points inside the
+// inner interval are the cell's: stored (unless the build reported an error: coincident particles have
+// the same cell, and the inner interval is taken as empty).  Points between the two are compared with
+// every neighbour by the reference's own squared distances, ties to the smaller id, and claimed
+// through a 64-bit atomic minimum on (global id, sorted index).  A point no cell claims (a failed
+// cell, or an axis with too few points to unwrap) is found by its own exact search.
 //
 // The kernel is bound by VALU issue (about 15 planes of 8 FP64 operations a round of 64 rows, with
 // the rows of a small cell filling half the lanes) and the latency of a cell's loads.  500k cells on
@@ -1111,8 +1111,8 @@ __global__ void __launch_bounds__(256) k_sample_claim(SampleArgs A) {
             const int32_t j0 = (int32_t)readlane_u32((uint32_t)j_l, i), cnt = (int32_t)readlane_u32((uint32_t)cnt_l, i);
             const int64_t row = (int64_t)(((uint64_t)readlane_u32((uint32_t)((uint64_t)row_l >> 32), i) << 32) |
                                           readlane_u32((uint32_t)(uint64_t)row_l, i));
-            const double x[3] = {readlane_d(x_l[0], i), readlane_d(x_l[1], i), readlane_d(x_l[2], i)};
-            const double R = readlane_d(R_l, i), R2 = R * R;
+            const double x[3] = {readlane_dbl(x_l[0], i), readlane_dbl(x_l[1], i), readlane_dbl(x_l[2], i)};
+            const double R = readlane_dbl(R_l, i), R2 = R * R;
             int f0[3], nf[3];
             for (int a = 0; a < 3; ++a) {
                 f0[a] = (int)readlane_u32((uint32_t)f0_l[a], i);

@@ -61,24 +61,6 @@ __device__ __forceinline__ double uni_d(double x) {
     return __longlong_as_double(((long long)(unsigned)hi << 32) | (unsigned)lo);
 }
 
-template <typename T>
-__device__ __forceinline__ T wave_max(T v) {
-    for (int o = 32; o > 0; o >>= 1) {
-        T u = __shfl_xor(v, o);
-        v = u > v ? u : v;
-    }
-    return v;
-}
-
-template <typename T>
-__device__ __forceinline__ T wave_min(T v) {
-    for (int o = 32; o > 0; o >>= 1) {
-        T u = __shfl_xor(v, o);
-        v = u < v ? u : v;
-    }
-    return v;
-}
-
 __device__ __forceinline__ double wave_sum_d(double v) {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
     return v;
@@ -197,7 +179,8 @@ __device__ __forceinline__ void bitonic_merge(uint32_t &k, int e, int size, bool
     if constexpr (J > 1) bitonic_merge<J / 2>(k, e, size, last);
 }
 
-// bitonic64 / bitonic128 with the cross-lane steps above (same networks, same results)
+// Bitonic sorts of 64 keys (one per lane) and of 128 (element 64 s + lane in k_s), ascending, with the
+// cross-lane steps above.
 __device__ __forceinline__ uint32_t bitonic64_x(uint32_t k) {
     const int l = lane_id();
     bitonic_merge<1>(k, l, 2, false);
@@ -288,45 +271,6 @@ __device__ __forceinline__ int next_segment(const uint32_t *counters, int64_t nc
     if (m == 0ull) return -1;
     const uint64_t after = m & ~((2ull << sg) - 1ull);
     return uni_i(__builtin_ctzll(after ? after : m));
-}
-
-// bitonic sort of 64 keys (one per lane), ascending by lane
-__device__ __forceinline__ uint32_t bitonic64(uint32_t k) {
-    int l = lane_id();
-    for (int size = 2; size <= 64; size <<= 1) {
-        for (int j = size >> 1; j > 0; j >>= 1) {
-            uint32_t o = (uint32_t)__shfl_xor((int)k, j);
-            bool up = (l & size) == 0 || size == 64;
-            bool lower = (l & j) == 0;
-            uint32_t mn = k < o ? k : o, mx = k < o ? o : k;
-            k = (lower == up) ? mn : mx;
-        }
-    }
-    return k;
-}
-
-// bitonic sort of 128 keys (element e = s * 64 + lane)
-__device__ __forceinline__ void bitonic128(uint32_t &k0, uint32_t &k1) {
-    int l = lane_id();
-    for (int size = 2; size <= 128; size <<= 1) {
-        for (int j = size >> 1; j > 0; j >>= 1) {
-            if (j == 64) {
-                uint32_t mn = k0 < k1 ? k0 : k1, mx = k0 < k1 ? k1 : k0;
-                k0 = mn;
-                k1 = mx;
-                continue;
-            }
-            uint32_t o0 = (uint32_t)__shfl_xor((int)k0, j);
-            uint32_t o1 = (uint32_t)__shfl_xor((int)k1, j);
-            bool lower = (l & j) == 0;
-            bool up0 = ((l & size) == 0);
-            bool up1 = (((64 + l) & size) == 0);
-            uint32_t mn0 = k0 < o0 ? k0 : o0, mx0 = k0 < o0 ? o0 : k0;
-            uint32_t mn1 = k1 < o1 ? k1 : o1, mx1 = k1 < o1 ? o1 : k1;
-            k0 = (lower == up0) ? mn0 : mx0;
-            k1 = (lower == up1) ? mn1 : mx1;
-        }
-    }
 }
 
 // bitonic sort of 64*N 64-bit keys, element e = s * 64 + lane
@@ -760,56 +704,5 @@ struct Poly {
             y = (double)vy[s];
             z = (double)vz[s];
         }
-    }
-
-    // Volume in FP64 without walking faces: the cone over face f from the seed
-    // is the sum of tetrahedra (seed, F_f, u, next_f(u)) over the vertices u of f,
-    // with F_f the foot of the seed on plane f; next_f(u) is the vertex that
-    // follows u counter-clockwise on f.  vp/vtri: LDS scratch of VMAX entries.
-    __device__ double volume(const Mem &S, double (*vp)[3]) const {
-        const int lane = lane_id();
-        const uint64_t mybit = 1ull << lane;
-#pragma unroll
-        for (int s = 0; s < VPL; ++s) {
-            if (in_mask(alive[s])) {
-                double x, y, z;
-                pos64(S, s, x, y, z);
-                vp[s * 64 + lane][0] = x;
-                vp[s * 64 + lane][1] = y;
-                vp[s * 64 + lane][2] = z;
-            }
-        }
-        wave_sync();
-        double acc = 0.0;
-#pragma unroll
-        for (int s = 0; s < VPL; ++s) {
-            if (!in_mask(alive[s])) continue;
-            const int u = s * 64 + lane;
-            const uint32_t t = vt[s];
-            const int f[3] = {(int)(t & 0xFF), (int)((t >> 8) & 0xFF), (int)((t >> 16) & 0xFF)};
-            const double *pu = vp[u];
-            for (int k = 0; k < 3; ++k) {
-                // on face f[k] the next vertex shares f[k] and f[k+2] (the face before f[k] in the triple)
-                const int fk = f[k], fc = f[(k + 2) % 3];
-                int w = -1;
-#pragma unroll
-                for (int ww = 0; ww < VPL; ++ww) {
-                    uint64_t x = S.fm[fk][ww] & S.fm[fc][ww];
-                    if (ww == s) x &= ~mybit;
-                    if (w < 0 && x) w = ww * 64 + __builtin_ctzll(x);
-                }
-                if (w < 0) continue;
-                const double *pw = vp[w];
-                const P4<double> &pl = S.pl64[fk];
-                double nn = pl.x * pl.x + pl.y * pl.y + pl.z * pl.z;
-                double sc = pl.d / nn;
-                double Fx = pl.x * sc, Fy = pl.y * sc, Fz = pl.z * sc;
-                double cx = pu[1] * pw[2] - pu[2] * pw[1];
-                double cy = pu[2] * pw[0] - pu[0] * pw[2];
-                double cz = pu[0] * pw[1] - pu[1] * pw[0];
-                acc += (Fx * cx + Fy * cy + Fz * cz) / 6.0;
-            }
-        }
-        return wave_sum_d(acc);
     }
 };

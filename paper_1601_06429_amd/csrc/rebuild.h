@@ -14,13 +14,6 @@
 #pragma once
 #include "poly.h"
 
-// a double held by lane l (l the same in every lane)
-__device__ __forceinline__ double readlane_d(double x, int l) {
-    const uint64_t u = (uint64_t)__double_as_longlong(x);
-    const uint64_t lo = readlane_u32((uint32_t)u, l), hi = readlane_u32((uint32_t)(u >> 32), l);
-    return __longlong_as_double((long long)((hi << 32) | lo));
-}
-
 template <typename PT4>
 __device__ __forceinline__ void gpos(const void *spos, int32_t j, double &x, double &y, double &z) {
     PT4 p = ((const PT4 *)spos)[j];

@@ -385,7 +385,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) k
             const int i = uni_i(__builtin_ctzll(m));
             const int64_t c = c0 + i;
             const int nf = (int)readlane_u32((uint32_t)nf_l, i), nv = (int)readlane_u32((uint32_t)nv_l, i);
-            const double sx = readlane_d(x_l, i), sy = readlane_d(y_l, i), sz = readlane_d(z_l, i);
+            const double sx = readlane_dbl(x_l, i), sy = readlane_dbl(y_l, i), sz = readlane_dbl(z_l, i);
             const DevItem &it = A.items[(int)readlane_u32((uint32_t)item_l, i)];
             auto readlane_i64 = [&](int64_t v) {
                 return (int64_t)(((uint64_t)readlane_u32((uint32_t)((uint64_t)v >> 32), i) << 32) |
