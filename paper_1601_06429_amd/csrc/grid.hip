@@ -703,12 +703,40 @@ __device__ __forceinline__ void grid_body(const GridArgs &A, char *smem, int wid
             // (Two rings, a lowest plane integrated by code without the chord, left two passes a cell
             // mostly idle once a face is integrated for both its cells: 24.2 ms at 2M/256^3.)
             int head = 0, qn = 0, rcur = 0;
+            // What a lowest plane's item adds besides G at its own plane: the full voxels below the face's
+            // x minimum, within the cell's own range, and the planes with the face entirely above them
+            // over R (classified with the same geometry and bound, so none is queued as well), from
+            // `first` on in steps of `step`.
+            auto emit_column = [&](int q, const ItemGeo &g, double A_, double G_, int first, int step) {
+                const int iend = min(g.mm, i1[0] + 1);
+                const int fl = S.flow[q];
+                const double fw = S.fw[q], full = g.hs * h[0] * A_;
+                for (int i = i0[0] + first; i < iend; i += step) emit(i, g.jj, g.kk, full * (i < fl ? wi : fw));
+                const double cy_ = -g.hs * S.fn[q][1] * h[1], cz_ = -g.hs * S.fn[q][2] * h[2];
+                const int npl = S.fpl[q][1];
+#pragma unroll 1
+                for (int p = 1 + first; p <= npl; p += step) {
+                    // geometry(q, p, rj, rk)'s X and e, the same expressions
+                    const int mp = S.fpl[q][0] + p - 1;
+                    const double Xp = mp * h[0] + del[0] - g0[0];
+                    const double ep = S.fn[q][3] - S.fn[q][0] * Xp - S.fn[q][1] * g.Y0 - S.fn[q][2] * g.Z0;
+                    if (g.hs * ep + fmin(0.0, cy_) + fmin(0.0, cz_) < 0.0) break;
+                    const double Gp = g.hs * (G_ + (g.X - Xp) * A_) * fw;
+                    emit(mp - 1, g.jj, g.kk, -Gp);
+                    emit(mp, g.jj, g.kk, Gp);
+                }
+            };
             auto integrate = [&](int take) {
                 wave_sync();
+                const uint64_t d = lane < take ? S.iq[(head + lane) & 127] : ~0ull;
+                const int q = (int)(d & 0xFFull), pi = (int)((d >> 8) & 0xFFFFull);
+                const int rj = (int)((d >> 24) & 0xFFFFFull), rk = (int)((d >> 44) & 0xFFFFFull);
+                // Each lane adds its own column, unless the columns are long and few of the pass's items
+                // have one: then the wavefront adds them together, one after another.
+                const uint64_t lowest = __ballot(pi == 0);
+                const bool together = bx > 2 * __popcll(lowest) + 16;
+                Reg Rg = {0.0, 0.0};
                 if (lane < take) {
-                    const uint64_t d = S.iq[(head + lane) & 127];
-                    const int q = (int)(d & 0xFFull), pi = (int)((d >> 8) & 0xFFFFull);
-                    const int rj = (int)((d >> 24) & 0xFFFFFull), rk = (int)((d >> 44) & 0xFFFFFull);
                     const ItemGeo g = geometry(q, pi, rj, rk);
                     const double nx_ = S.fn[q][0], ny_ = S.fn[q][1], nz_ = S.fn[q][2];
                     const double hs = g.hs, rnx = 1.0 / nx_;
@@ -716,36 +744,23 @@ __device__ __forceinline__ void grid_body(const GridArgs &A, char *smem, int wid
                     // a face's lowest plane clips nothing of it: the chord is taken one plane further
                     // down, clear of the face (X itself may round to either side of its x minimum)
                     const double eH = pi == 0 ? fma(nx_, h[0], g.e) : g.e;
-                    const Reg Rg = region_integrals<VPL>(S, o, m, g.Y0, g.Z0, h[1], h[2], ih[1], ih[2], hs, eH, ny_, nz_, g.X, rnx);
-                    const double fw = S.fw[q];
-                    const double G = hs * Rg.G * fw;
+                    Rg = region_integrals<VPL>(S, o, m, g.Y0, g.Z0, h[1], h[2], ih[1], ih[2], hs, eH, ny_, nz_, g.X, rnx);
+                    const double G = hs * Rg.G * S.fw[q];
                     if (pi > 0) {
                         emit(g.mm - 1, g.jj, g.kk, -G);
                         emit(g.mm, g.jj, g.kk, G);
                     } else if (Rg.A != 0.0) {
-                        // full voxels below the face's x minimum, within the cell's own range
-                        const int iend = min(g.mm, i1[0] + 1);
-                        const int fl = S.flow[q];
-                        const double full = hs * h[0] * Rg.A;
-                        for (int i = i0[0]; i < iend; ++i) emit(i, g.jj, g.kk, full * (i < fl ? wi : fw));
                         emit(g.mm, g.jj, g.kk, G);
-                        // the planes with the face entirely above them over R (classified
-                        // with the same geometry and bound, so none is queued as well)
-                        const double cy_ = -hs * ny_ * h[1], cz_ = -hs * nz_ * h[2];
-                        const int npl = S.fpl[q][1];
-#pragma unroll 1
-                        for (int p = 1; p <= npl; ++p) {
-                            // geometry(q, p, rj, rk)'s X and e, the same expressions
-                            const int mp = S.fpl[q][0] + p - 1;
-                            const double Xp = mp * h[0] + del[0] - g0[0];
-                            const double ep = S.fn[q][3] - S.fn[q][0] * Xp - S.fn[q][1] * g.Y0 - S.fn[q][2] * g.Z0;
-                            if (hs * ep + fmin(0.0, cy_) + fmin(0.0, cz_) < 0.0) break;
-                            const double Gp = hs * (Rg.G + (g.X - Xp) * Rg.A) * fw;
-                            emit(mp - 1, g.jj, g.kk, -Gp);
-                            emit(mp, g.jj, g.kk, Gp);
-                        }
+                        if (!together) emit_column(q, g, Rg.A, Rg.G, 0, 1);
                     }
                 }
+                if (together)
+                    for (uint64_t m = lowest & __ballot(Rg.A != 0.0); m; m &= m - 1) {
+                        const int l = uni_i(__builtin_ctzll(m));
+                        const int ql = (int)readlane_u32((uint32_t)q, l);
+                        const ItemGeo g = geometry(ql, 0, (int)readlane_u32((uint32_t)rj, l), (int)readlane_u32((uint32_t)rk, l));
+                        emit_column(ql, g, readlane_dbl(Rg.A, l), readlane_dbl(Rg.G, l), lane, 64);
+                    }
                 head += take;
                 qn -= take;
                 wave_sync();
