@@ -80,9 +80,11 @@ __device__ __forceinline__ int dec_bin(const double *thr, int n_thr, double d) {
 }
 
 // The histogram has few entries and every particle adds to several, so the blocks (as many as the CUs
-// hold, each taking many particles) count in LDS and add their totals once; a histogram larger than
-// that is counted with global atomics.  262k particles in 8 slabs: 1.04 ms with a global atomic per
-// entry, 30 us.
+// hold, each taking many particles) count in LDS and add their totals once.  A histogram larger than
+// that is counted with global atomics, and so is one with more entries than there are particles, which
+// every block would clear and add for few counts.  262k particles in 8 slabs: 1.04 ms with a global
+// atomic per entry, 30 us; whole calls, LDS | global: 3000 particles, 64 tasks (18432 entries) 222 |
+// 206 us, 30000 123 | 136.
 #define DEC_LDS_HIST (32 * 1024)  // entries (128 KB)
 
 template <typename T>
@@ -390,12 +392,13 @@ vt_status decompose(vt_ctx *c, const T *pos, int64_t n, const DecGeo &g, const v
     e = hipMemcpyAsync(c->dec_thr, thr.data(), sizeof(double) * n_thr, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = vt_launch_zero_u32(c->dec_hist, n_hist, s);
     if (e != hipSuccess) return dec_err(e);
-    const bool lds = n_hist <= DEC_LDS_HIST;
+    const bool lds = n_hist <= DEC_LDS_HIST && n > n_hist;
     const size_t lds_bytes = lds ? sizeof(uint32_t) * (size_t)n_hist : 0;
     int ncu = 0;
     hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, c->device);
     if (ncu <= 0) ncu = 256;
-    e = hipFuncSetAttribute((const void *)k_dec_slab<T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+    e = hipFuncSetAttribute((const void *)k_dec_slab<T>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)sizeof(uint32_t) * DEC_LDS_HIST);
     if (e != hipSuccess) return dec_err(e);
     const int per_cu = lds_bytes > 40 * 1024 ? 1 : 4;
     const int64_t blocks = std::min<int64_t>((n + 255) / 256, lds ? (int64_t)ncu * per_cu : INT32_MAX);
