@@ -912,6 +912,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
 // 192^3 points took 3.00 ms with every candidate point tested against the neighbours one by one and
 // take 0.76 ms; 100k cells on 240 x 216 x 192 points (27 a voxel) took 8.4-10.5 ms in tiles of points
 // that shared a list of candidate particles and take 0.54 ms.
+#define VT_SAMPLE_DENSE 4096  // candidates of a tile above which it leaves the points to the cells
 #define VT_CLAIM_NBR 136    // faces staged per cell (the large clip kernel keeps no more)
 
 struct SampleArgs {
@@ -930,7 +931,9 @@ struct SampleArgs {
     const int32_t *ctopo;       // topology records: face tags first
     const int32_t *cnf;         // faces in the record (0: no record)
     const int32_t *cnv;         // vertices of the cell
-    const uint32_t *counters;
+    uint32_t *counters;
+    int64_t npos;               // sorted particles
+    double r0;                  // tiles: first widening (the mean inter-particle distance), 0: no tiles
     int64_t ncells;
     const double *value;
     double *grid;
@@ -956,6 +959,13 @@ __device__ __forceinline__ double sample_coord32(const DevItem &it, int a, int d
 
 // i in [-n, 2n) to [0, n)
 __device__ __forceinline__ int wrap_once(int i, int n) { return i < 0 ? i + n : (i >= n ? i - n : i); }
+
+struct SampleMem {
+    int32_t rb[512];    // covering cells: range starts
+    int32_t rp[513];    // prefix of range lengths
+    double px[64], py[64], pz[64];
+    int32_t pg[64], pj[64];
+};
 
 __device__ __forceinline__ int32_t lower_key(const uint64_t *skey, int32_t a, int32_t c, uint64_t k) {
     while (a < c) {
@@ -1076,6 +1086,7 @@ __global__ void __launch_bounds__(256) k_sample_claim(SampleArgs A) {
     const int64_t F[3] = {(int64_t)A.nx * sub, (int64_t)A.ny * sub, (int64_t)A.nz * sub};
     const double invL[3] = {uni_d(1.0 / it.L[0]), uni_d(1.0 / it.L[1]), uni_d(1.0 / it.L[2])};
     const double ihf[3] = {uni_d((double)F[0] / it.L[0]), uni_d((double)F[1] / it.L[1]), uni_d((double)F[2] / it.L[2])};
+    if (A.r0 > 0.0 && A.counters[CTR_SAMP_LEFT] == 0) return;  // the tiles have taken every point
     const bool clean = A.counters[CTR_STATUS] == 0;
     const double zend = uni_d(1e-7 + 1e-15 * (fabs(it.lo[2]) + it.S) * ihf[2]);
     // each XCD (blocks are dealt to them in turn) takes one contiguous eighth of the Morton order
@@ -1220,11 +1231,178 @@ __global__ void __launch_bounds__(256) k_sample_claim(SampleArgs A) {
     }
 }
 
+// Several points a voxel, up to about eight points a cell, and particles spread evenly: a wavefront
+// takes a 4 x 4 x 4 tile of points (a lane each) and scans one list of candidates for all of them, the
+// particles of the Morton cells that cover the tile widened by r, staged through LDS 64 at a time.  A
+// lane is done when its best distance is below its distance to the sides of the covered cells less two
+// key quanta, otherwise r doubles.  The cost goes with the points, not the cells, but next to clumps
+// and in voids with the candidates as well, by hundreds: where k_sample_clear finds the particles
+// uneven the tiles are left out, and a tile that finds more than an even distribution would put there
+// ends them; then the cells claim the points.  Tiles | cells: 1M uniform cells, two points along a
+// voxel's side, 64^3 points 278 | 1324 us, 192^3 1404 | 1605; 300k, 64^3 110 | 457; 100k, 96^3 (beyond
+// the rule) 261 | 178; 262k clustered cells, 64^3 20100 | 351.
+template <typename PT4>
+__global__ void __launch_bounds__(256) k_sample_tiles(SampleArgs A) {
+    extern __shared__ char smem[];
+    SampleMem &S = *reinterpret_cast<SampleMem *>(smem + (size_t)(threadIdx.x >> 6) * sizeof(SampleMem));
+    const int lane = threadIdx.x & 63;
+    const uint64_t lt = (1ull << lane) - 1ull;
+    const DevItem it = uniform_item(A.items[0]);
+    const int sub = A.sub;
+    const int64_t fd[3] = {(int64_t)A.nx * sub, (int64_t)A.ny * sub, (int64_t)A.nz * sub};
+    const int64_t ntile[3] = {(fd[0] + 3) / 4, (fd[1] + 3) / 4, (fd[2] + 3) / 4};
+    const int64_t n_tiles = ntile[0] * ntile[1] * ntile[2];
+    const int dims[3] = {A.nx, A.ny, A.nz};
+    const double quantum = it.S / (double)(1 << VT_MORTON_BITS);
+    const double invL[3] = {1.0 / it.L[0], 1.0 / it.L[1], 1.0 / it.L[2]};
+    const int64_t nwaves = (int64_t)gridDim.x * (blockDim.x >> 6);
+    for (int64_t t = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); t < n_tiles; t += nwaves) {
+        if (uni_i((int)__hip_atomic_load(&A.counters[CTR_SAMP_LEFT], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) return;
+        const int64_t tz = t % ntile[2], ty = (t / ntile[2]) % ntile[1], tx = t / (ntile[1] * ntile[2]);
+        const int64_t f[3] = {tx * 4 + (lane >> 4), ty * 4 + ((lane >> 2) & 3), tz * 4 + (lane & 3)};
+        const bool valid = f[0] < fd[0] && f[1] < fd[1] && f[2] < fd[2];
+        // the sample point: voxel i, sub-cell s (the reference's expression)
+        double q[3], tlo[3], thi[3];
+        for (int a = 0; a < 3; ++a) {
+            const double h = it.L[a] / dims[a];
+            const int64_t fa = valid ? f[a] : 0;
+            q[a] = it.lo[a] + ((double)(fa / sub) + ((double)(fa % sub) + 0.5) / (double)sub) * h;
+            // the tile's extent: its first and last points along a
+            const int64_t f0 = (a == 0 ? tx : a == 1 ? ty : tz) * 4;
+            const int64_t f1 = min(f0 + 3, fd[a] - 1);
+            tlo[a] = it.lo[a] + ((double)(f0 / sub) + ((double)(f0 % sub) + 0.5) / (double)sub) * h;
+            thi[a] = it.lo[a] + ((double)(f1 / sub) + ((double)(f1 % sub) + 0.5) / (double)sub) * h;
+        }
+        double best = 1e300;
+        int32_t bg = 0x7FFFFFFF, bj = -1;
+        bool left = false;
+        for (double r = A.r0;; r *= 2.0) {
+            // covering Morton cells: side c >= r (coarser while more than 512 would be needed)
+            int l = 0;
+            double c = it.S;
+            while (l < VT_MORTON_BITS && 0.5 * c >= r) {
+                c *= 0.5;
+                ++l;
+            }
+            int64_t a0[3], na[3];
+            bool whole[3];
+            for (;;) {
+                const int64_t ncl = 1ll << l;
+                for (int a = 0; a < 3; ++a) {
+                    int64_t i0 = (int64_t)floor((tlo[a] - r - it.lo[a]) / c);
+                    int64_t i1 = (int64_t)floor((thi[a] + r - it.lo[a]) / c);
+                    whole[a] = i1 - i0 + 1 >= ncl;
+                    if (whole[a]) {
+                        i0 = 0;
+                        i1 = ncl - 1;
+                    }
+                    a0[a] = i0;
+                    na[a] = i1 - i0 + 1;
+                }
+                if (na[0] * na[1] * na[2] <= 512 || l == 0) break;
+                --l;
+                c *= 2.0;
+            }
+            // the lane's reach: its distance to the nearest side of the covered cells (axes not
+            // covered whole), less two key quanta for the rounding of particle keys
+            double reach = 1e300;
+            for (int a = 0; a < 3; ++a)
+                if (!whole[a]) {
+                    const double b0 = it.lo[a] + (double)a0[a] * c, b1 = it.lo[a] + (double)(a0[a] + na[a]) * c;
+                    reach = fmin(reach, fmin(q[a] - b0, b1 - q[a]));
+                }
+            reach -= 2.0 * quantum;
+            const int64_t ncl = 1ll << l;
+            const int ncells = (int)(na[0] * na[1] * na[2]);
+            int count = 0;
+            for (int base = 0; base < ncells; base += 64) {
+                const int k = base + lane;
+                int32_t cb = 0, ce = 0;
+                if (k < ncells) {
+                    const int64_t u[3] = {a0[0] + k % na[0], a0[1] + (k / na[0]) % na[1], a0[2] + k / (na[0] * na[1])};
+                    const uint64_t cx = (uint64_t)((u[0] % ncl + ncl) % ncl), cy = (uint64_t)((u[1] % ncl + ncl) % ncl),
+                                   cz = (uint64_t)((u[2] % ncl + ncl) % ncl);
+                    morton_range(A, it, l, vt_morton(cx, cy, cz), cb, ce);
+                }
+                const bool keep = ce > cb;
+                const uint64_t km = __ballot(keep);
+                if (keep) {
+                    const int slot = count + __popcll(km & lt);
+                    S.rb[slot] = cb;
+                    S.rp[slot] = ce - cb;
+                }
+                count += __popcll(km);
+            }
+            wave_sync();
+            int carry = 0;
+            for (int base = 0; base < count; base += 64) {
+                const int k = base + lane;
+                const int len = k < count ? S.rp[k] : 0;
+                int tot;
+                const int pre = wave_excl_scan(len, &tot);
+                if (k < count) S.rp[k] = carry + pre;
+                carry += tot;
+            }
+            if (lane == 0) S.rp[count] = carry;
+            wave_sync();
+            const int total = carry;
+            // more than a uniform distribution puts there: all points are left to the cells
+            const double even = (double)A.npos * (double)ncells / (double)(ncl * ncl * ncl);
+            if ((double)total > 3.0 * even + 64.0 || total > VT_SAMPLE_DENSE) {
+                left = true;
+                break;
+            }
+            for (int c0 = 0; c0 < total; c0 += 64) {
+                const int fi = c0 + lane;
+                if (fi < total) {
+                    int lo = 0, hi = count - 1;
+                    while (lo < hi) {
+                        const int mid = (lo + hi + 1) >> 1;
+                        if (S.rp[mid] <= fi) lo = mid; else hi = mid - 1;
+                    }
+                    const int32_t j = S.rb[lo] + (fi - S.rp[lo]);
+                    double px, py, pz;
+                    gpos<PT4>(A.spos, j, px, py, pz);
+                    S.px[lane] = px;
+                    S.py[lane] = py;
+                    S.pz[lane] = pz;
+                    S.pg[lane] = A.sgid[j];
+                    S.pj[lane] = j;
+                }
+                wave_sync();
+                const int nc = min(64, total - c0);
+                for (int k = 0; k < nc; ++k) {
+                    double ex = S.px[k] - q[0], ey = S.py[k] - q[1], ez = S.pz[k] - q[2];
+                    ex -= it.L[0] * rint(ex * invL[0]);
+                    ey -= it.L[1] * rint(ey * invL[1]);
+                    ez -= it.L[2] * rint(ez * invL[2]);
+                    const double d2 = ex * ex + ey * ey + ez * ez;
+                    const int32_t gj = S.pg[k];
+                    if (d2 < best || (d2 == best && gj < bg)) {
+                        best = d2;
+                        bg = gj;
+                        bj = S.pj[k];
+                    }
+                }
+                wave_sync();
+            }
+            const bool done = (whole[0] && whole[1] && whole[2]) || (bj >= 0 && reach > 0.0 && best < reach * reach);
+            if (__ballot(valid && !done) == 0ull) break;
+        }
+        if (left) {
+            if (lane == 0) atomicOr(&A.counters[CTR_SAMP_LEFT], 1u);
+            return;
+        }
+        if (valid) A.slot[(f[0] * fd[1] + f[1]) * fd[2] + f[2]] = ((unsigned long long)(uint32_t)bg << 32) | (uint32_t)bj;
+    }
+}
+
 // Points no cell claimed get their own exact search; with one point per voxel the voxel's
 // value is written here too.
 template <typename PT4>
 __global__ void k_sample_fixup(SampleArgs A) {
     const int sub = A.sub;
+    if (A.r0 > 0.0 && A.counters[CTR_SAMP_LEFT] == 0) return;  // the tiles have taken every point
     const int64_t F[3] = {(int64_t)A.nx * sub, (int64_t)A.ny * sub, (int64_t)A.nz * sub};
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= F[0] * F[1] * F[2]) return;
@@ -1248,9 +1426,18 @@ __global__ void k_sample_fixup(SampleArgs A) {
     }
 }
 
-__global__ void k_fill_u64(unsigned long long *p, int64_t n, unsigned long long v) {
+// No point claimed yet.  With tiles (probe: a level of the Morton cells, 24 to 192 particles in each on
+// average), also whether the particles are spread evenly, for in a clump's tiles are slow even where a
+// tile finds no more than it can take.
+__global__ void k_sample_clear(SampleArgs A, int64_t nfine, int probe) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
+    if (i < nfine) A.slot[i] = ~0ull;
+    if (probe > 0 && i < (1ll << (3 * probe))) {
+        int32_t b, e;
+        morton_range(A, A.items[0], probe, (uint64_t)i, b, e);
+        if ((double)(e - b) > 3.0 * (double)A.npos / (double)(1ll << (3 * probe)) + 32.0)
+            atomicOr(&A.counters[CTR_SAMP_LEFT], 1u);
+    }
 }
 
 // sub > 1: each voxel averages its sub^3 points in the reference's order
@@ -1270,6 +1457,7 @@ __global__ void k_sample_average(SampleArgs A) {
                 acc += A.value[A.srow[(int32_t)(last & 0xFFFFFFFFull)]];
             }
     A.grid[v] = acc / (double)(sub * sub * sub);
+    if (v == 0) A.counters[CTR_SAMP_LEFT] = 0u;  // as the build and every call leave it
     if (A.nearest) A.nearest[v] = (int32_t)(last >> 32);
 }
 
@@ -1292,6 +1480,7 @@ hipError_t vt_launch_grid_sample(vt_ctx *c, const double *value, int nx, int ny,
     a.cnf = c->cnf;
     a.cnv = c->cnv;
     a.counters = c->counters;
+    a.npos = c->n_total;
     a.ncells = c->n_owned;
     a.value = value;
     a.grid = grid;
@@ -1315,7 +1504,25 @@ hipError_t vt_launch_grid_sample(vt_ctx *c, const double *value, int nx, int ny,
     int ncu = 0;
     hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, c->device);
     if (ncu <= 0) ncu = 256;
-    k_fill_u64<<<(unsigned)((nfine + tpb - 1) / tpb), tpb, 0, c->stream>>>(a.slot, nfine, ~0ull);
+    // Tiles of points where they are quicker than the cells (k_sample_tiles).  Few points are bound by the
+    // latency of a tile, few cells are quickly gone through, and from some eight points a cell on the
+    // cells' rows are cheaper than the tiles' lists.  Uniform cells, two points along a voxel's side,
+    // tiles | cells in us: 100k cells, 4096 points 281 | 78, 32768 131 | 157; 30k, 32768 92 | 58; 300k,
+    // 32768 464 | 378, 110592 276 | 443; 1M, 32768 361 | 456; 300k, 7 points a cell 280 | 491, 24 865 | 545.
+    const bool tiles = sub > 1 && nfine >= 32768 && a.ncells >= 65536 && nfine <= 8 * a.ncells;
+    int probe = 0;
+    while (tiles && (24ll << (3 * (probe + 1))) <= a.npos) ++probe;
+    const int64_t nclear = std::max<int64_t>(nfine, 1ll << (3 * probe));
+    const DevItem &it = c->h_items[0];
+    a.r0 = tiles ? cbrt(it.L[0] * it.L[1] * it.L[2] / (double)c->n_total) : 0.0;
+    k_sample_clear<<<(unsigned)((nclear + tpb - 1) / tpb), tpb, 0, c->stream>>>(a, nfine, probe);
+    if (tiles) {
+        const int64_t nt = ((int64_t)nx * sub + 3) / 4 * (((int64_t)ny * sub + 3) / 4) * (((int64_t)nz * sub + 3) / 4);
+        const unsigned tb = (unsigned)std::min<int64_t>((nt + 3) / 4, (int64_t)ncu * 64);
+        const size_t lds = sizeof(SampleMem) * 4;
+        if (c->dtype == VT_F32) k_sample_tiles<float4><<<tb, 256, lds, c->stream>>>(a);
+        else k_sample_tiles<double4><<<tb, 256, lds, c->stream>>>(a);
+    }
     // six blocks of four wavefronts per CU, a multiple of the XCDs; as many cells at a time as leave
     // every wavefront a turn
     const int64_t blocks = ((int64_t)ncu * 6 + VT_XCD_SEGMENTS - 1) / VT_XCD_SEGMENTS * VT_XCD_SEGMENTS;

@@ -37,6 +37,7 @@
 #define CTR_STRUCT_SLOW 4  // structure output: cells that need more than their record
 #define CTR_REC_REJECT 12  // topology records that failed their checks (a clip-kernel fault; 0 expected)
 #define CTR_TAB_PIECES 13  // level table: pieces of long runs listed for k_level_fill
+#define CTR_SAMP_LEFT 14   // sampling: a tile of points has left them to the cells
 // Work counters of the XCD segments (fast clip kernel, grid deposit), each in a 128-byte line of its
 // own, with the facet count of the segment's cells.  Atomics of all wavefronts on one line queue up
 // behind one another: with the eight counters and the facet count in one line the clip of 2M cells
