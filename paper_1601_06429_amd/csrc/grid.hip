@@ -179,14 +179,18 @@ __device__ __forceinline__ void slab(double a, double b, double ib, double lo, d
 // D = Omega ∩ R ∩ H in coordinates relative to R's corner (Y0, Z0): Omega the
 // counter-clockwise loop lp[o .. o+m) of seed-relative vertices,
 // R = [Y0, Y0 + hy] x [Z0, Z0 + hz], H = {hs (e - ny y - nz z) > 0} (the
-// part of the face above x = X), with e given for the shifted coordinates and
-// rnx = 1 / n_x.  One pass over Omega's edges clips each edge to R ∩ H and, for
+// part of the face above x = X) or, without `cut`, the whole plane, with e given
+// for the shifted coordinates and rnx = 1 / n_x.  (H has to be left out by itself:
+// a plane clear of the face would do for the edges, but nothing keeps its chord
+// out of a face whose edges all have length zero, as cells of a lattice have.)  One pass over Omega's edges clips each edge to R ∩ H and, for
 // every edge, restricts R's four edges and the chord to its inner side; those
 // segments are integrated after the pass.
 template <int VPL>
 __device__ __forceinline__ Reg region_integrals(const GridMem<VPL> &S, int o, int m, double Y0, double Z0, double hy, double hz,
-                                double ihy, double ihz, double hs, double e, double ny, double nz, double X, double rnx) {
+                                double ihy, double ihz, bool cut, double hs_, double e, double ny, double nz, double X,
+                                double rnx) {
     Reg D = {0.0, 0.0};
+    const double hs = cut ? hs_ : 0.0;  // without H, gH is zero: inside
     auto gH = [&](double y, double z) { return hs * (e - ny * y - nz * z); };
     const double Oy = S.lp[o][1] - Y0, Oz = S.lp[o][2] - Z0, gO = S.lp[o][0] - X;
     auto tri = [&](double y0, double z0, double g0, double y1, double z1, double g1) {
@@ -284,7 +288,7 @@ __device__ __forceinline__ Reg region_integrals(const GridMem<VPL> &S, int o, in
         }
     }
     // (c) the chord inside Omega ∩ R
-    if (ct0 < ct1) {
+    if (cut && ct0 < ct1) {
         const double ey = cy1 - cy0, ez = cz1 - cz0;
         tri(cy0 + ct0 * ey, cz0 + ct0 * ez, 0.0, cy0 + ct1 * ey, cz0 + ct1 * ez, 0.0);
     }
@@ -741,10 +745,9 @@ __device__ __forceinline__ void grid_body(const GridArgs &A, char *smem, int wid
                     const double nx_ = S.fn[q][0], ny_ = S.fn[q][1], nz_ = S.fn[q][2];
                     const double hs = g.hs, rnx = 1.0 / nx_;
                     const int o = S.loff[q], m = S.loff[q + 1] - o;
-                    // a face's lowest plane clips nothing of it: the chord is taken one plane further
-                    // down, clear of the face (X itself may round to either side of its x minimum)
-                    const double eH = pi == 0 ? fma(nx_, h[0], g.e) : g.e;
-                    Rg = region_integrals<VPL>(S, o, m, g.Y0, g.Z0, h[1], h[2], ih[1], ih[2], hs, eH, ny_, nz_, g.X, rnx);
+                    // a face's lowest plane clips nothing of it (X may round to either side of its x minimum)
+                    Rg = region_integrals<VPL>(S, o, m, g.Y0, g.Z0, h[1], h[2], ih[1], ih[2], pi > 0, hs, g.e, ny_, nz_,
+                                               g.X, rnx);
                     const double G = hs * Rg.G * S.fw[q];
                     if (pi > 0) {
                         emit(g.mm - 1, g.jj, g.kk, -G);
