@@ -1234,16 +1234,15 @@ __global__ void __launch_bounds__(256) k_sample_claim(SampleArgs A) {
     }
 }
 
-// Several points a voxel, up to about eight points a cell, and particles spread evenly: a wavefront
-// takes a 4 x 4 x 4 tile of points (a lane each) and scans one list of candidates for all of them, the
-// particles of the Morton cells that cover the tile widened by r, staged through LDS 64 at a time.  A
-// lane is done when its best distance is below its distance to the sides of the covered cells less two
-// key quanta, otherwise r doubles.  The cost goes with the points, not the cells, but next to clumps
-// and in voids with the candidates as well, by hundreds: where k_sample_clear finds the particles
-// uneven the tiles are left out, and a tile that finds more than an even distribution would put there
-// ends them; then the cells claim the points.  Tiles | cells: 1M uniform cells, two points along a
-// voxel's side, 64^3 points 278 | 1324 us, 192^3 1404 | 1605; 300k, 64^3 110 | 457; 100k, 96^3 (beyond
-// the rule) 261 | 178; 262k clustered cells, 64^3 20100 | 351.
+// Several points a voxel, few points a cell, and particles spread evenly (the rule: vt_launch_grid_sample):
+// a wavefront takes a 4 x 4 x 4 tile of points (a lane each) and scans one list of candidates for all of
+// them, the particles of the Morton cells that cover the tile widened by r, staged through LDS 64 at a
+// time.  A lane is done when its best distance is below its distance to the sides of the covered cells
+// less two key quanta, otherwise r doubles.  The cost goes with the points, not the cells, but next to
+// clumps and in voids with the candidates as well, by hundreds: where k_sample_clear finds the
+// particles uneven the tiles are left out, and a tile that finds more than an even distribution would
+// put there ends them; then the cells claim the points (262k clustered cells, 64^3 points: 20.1 ms by
+// tiles, 0.35 by cells).
 template <typename PT4>
 __global__ void __launch_bounds__(256) k_sample_tiles(SampleArgs A) {
     extern __shared__ char smem[];
@@ -1507,12 +1506,22 @@ hipError_t vt_launch_grid_sample(vt_ctx *c, const double *value, int nx, int ny,
     int ncu = 0;
     hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, c->device);
     if (ncu <= 0) ncu = 256;
-    // Tiles of points where they are quicker than the cells (k_sample_tiles).  Few points are bound by the
-    // latency of a tile, few cells are quickly gone through, and from some eight points a cell on the
-    // cells' rows are cheaper than the tiles' lists.  Uniform cells, two points along a voxel's side,
-    // tiles | cells in us: 100k cells, 4096 points 281 | 78, 32768 131 | 157; 30k, 32768 92 | 58; 300k,
-    // 32768 464 | 378, 110592 276 | 443; 1M, 32768 361 | 456; 300k, 7 points a cell 280 | 491, 24 865 | 545.
-    const bool tiles = sub > 1 && nfine >= 32768 && a.ncells >= 65536 && nfine <= 8 * a.ncells;
+    // Tiles of points where they are quicker than the cells (k_sample_tiles), which takes many cells and
+    // enough points for their number of tiles, but few of them a cell, and a grid that is no more than
+    // twice as fine along one axis as along another (across a flat grid's spacing few cells hold points).
+    // Tiles that line up with the Morton cells, powers of two, find their points' nearest particles with
+    // the first list, others take a second one.  Uniform cells, tiles | cells in us:
+    //   64^3 points   70k cells 70 | 120, 150k 160 | 285, 300k 116 | 457, 1M 283 | 1324
+    //   64 x 32 x 64  45k 160 | 76, 150k 143 | 228 (32 x 64 x 32), 300k 328 | 468, 1M 316 | 926
+    //   32^3          100k 135 | 157, 300k 468 | 378, 450k 644 | 417, 1M 365 | 456;  128^3  100k 262 | 191
+    //   odd sizes     220k, 0.2 to 4 points a cell 362..662 | 311..351, 300k, 0.3 to 2.6 248..365 | 429..477
+    //                 and 5.8 489 | 475, 450k 0.14 537 | 546, 4.6 623 | 630, 1M 0.09 755 | 1000, 4.2 1406 | 1485
+    const int64_t F[3] = {(int64_t)nx * sub, (int64_t)ny * sub, (int64_t)nz * sub};
+    const int64_t fmin = std::min(F[0], std::min(F[1], F[2])), fmax = std::max(F[0], std::max(F[1], F[2]));
+    const bool aligned = !(F[0] & (F[0] - 1)) && !(F[1] & (F[1] - 1)) && !(F[2] & (F[2] - 1));
+    const bool tiles = sub > 1 && fmax <= 2 * fmin &&
+                       (aligned ? a.ncells >= 65536 && nfine >= 65536 && nfine <= 8 * a.ncells
+                                : a.ncells >= 300000 && nfine >= 90000 && nfine <= 4 * a.ncells);
     int probe = 0;
     while (tiles && (24ll << (3 * (probe + 1))) <= a.npos) ++probe;
     const int64_t nclear = std::max<int64_t>(nfine, 1ll << (3 * probe));
@@ -1520,7 +1529,7 @@ hipError_t vt_launch_grid_sample(vt_ctx *c, const double *value, int nx, int ny,
     a.r0 = tiles ? cbrt(it.L[0] * it.L[1] * it.L[2] / (double)c->n_total) : 0.0;
     k_sample_clear<<<(unsigned)((nclear + tpb - 1) / tpb), tpb, 0, c->stream>>>(a, nfine, probe);
     if (tiles) {
-        const int64_t nt = ((int64_t)nx * sub + 3) / 4 * (((int64_t)ny * sub + 3) / 4) * (((int64_t)nz * sub + 3) / 4);
+        const int64_t nt = (F[0] + 3) / 4 * ((F[1] + 3) / 4) * ((F[2] + 3) / 4);
         const unsigned tb = (unsigned)std::min<int64_t>((nt + 3) / 4, (int64_t)ncu * 64);
         const size_t lds = sizeof(SampleMem) * 4;
         if (c->dtype == VT_F32) k_sample_tiles<float4><<<tb, 256, lds, c->stream>>>(a);

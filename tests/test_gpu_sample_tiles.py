@@ -1,6 +1,7 @@
 """Sampling several points a voxel with about as many points as cells, on both sides of the rule that
-chooses tiles of points (65536 cells, 32768 points, eight points a cell): evenly spread particles,
-tiles cut off by the grid's end, a clump that leaves the points to the cells (one that shows in the
+chooses tiles of points (powers of two: 65536 cells and points, eight points a cell; other sizes:
+300000 cells; twice as fine along one axis as along another): evenly spread particles, tiles cut off by
+the grid's end, a clump that leaves the points to the cells (one that shows in the
 counts of Morton cells, and a tight one of a few hundred particles among many that does not), and a
 lattice whose points have eight nearest particles.  Values are the particles' indices, whose sums over
 a voxel are exact, and ids come from a k-d tree, so the averages are equal wherever no other particle
@@ -32,8 +33,10 @@ def _sample(vt, torch_cuda, p, dims, sub):
 
 
 @pytest.mark.parametrize("kind", ["even", "clump", "tight"])
-@pytest.mark.parametrize("n,dims,sub", [(65535, (16, 16, 16), 2), (65536, (16, 16, 16), 2), (65536, (16, 16, 15), 2),
-                                        (70001, (5, 41, 23), 3), (66000, (63, 32, 33), 2), (140000, (20, 9, 31), 4)])
+@pytest.mark.parametrize("n,dims,sub", [(65535, (32, 16, 16), 2), (65536, (32, 16, 16), 2), (65536, (16, 16, 15), 2),
+                                        (70001, (16, 16, 8), 4), (32769, (32, 32, 32), 2), (299999, (22, 23, 24), 2),
+                                        (300000, (22, 23, 24), 2), (300000, (15, 21, 13), 3), (310000, (44, 22, 23), 2),
+                                        (310000, (45, 22, 23), 2)])
 @pytest.mark.parametrize("dtype", [np.float32, np.float64])
 def test_against_kdtree(vt, torch_cuda, n, dims, sub, kind, dtype):
     rng = np.random.default_rng(n)
