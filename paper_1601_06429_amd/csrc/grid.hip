@@ -23,13 +23,13 @@
 // (value / voxel volume).  That needs both cells to have the face, as cells rebuilt from their
 // topology records do.  A cell rebuilt from its facet list lacks the faces below its own facet
 // threshold, which need not be small for its neighbour: such a cell integrates all its faces, and its
-// neighbours theirs towards it.  The kernel is bound by VALU issue at two wavefronts per SIMD (237 vector
-// registers, 19 KB of LDS each), so halving the integrals, the face loops and the classification is
-// what counts: 2M cells on 256^3 took 29.5 ms with every face integrated from both sides and take
-// 22.4 ms now (region integrals 9.0, classifying and emitting 5.1, face loops 2.9, choosing the
-// faces and the cell's extent 2.0, rebuilding 2.3, dealing cells 0.7, by copies that leave steps
-// out); 5003 cells on 41 x 29 x 50, 0.67 -> 0.13 ms, most of it from taking one cell at a time
-// instead of 16 where 16 leave wavefronts without work.
+// neighbours theirs towards it.  The kernel is bound by VALU issue at two wavefronts per SIMD (256
+// vector registers, 19 KB of LDS each), so halving the integrals, the face loops and the
+// classification is what counts: 2M cells on 256^3 took 29.5 ms with every face integrated from both
+// sides, 22.4 ms with faces shared (region integrals 9.0, classifying and emitting 5.1, face loops
+// 2.9, choosing the faces and the cell's extent 2.0, rebuilding 2.3, dealing cells 0.7, by copies that
+// leave steps out) and take 21.9 now; 5003 cells on 41 x 29 x 50, 0.67 -> 0.13 ms, most of it from
+// taking one cell at a time instead of 16 where 16 leave wavefronts without work.
 //
 // The grid lines are evaluated at X_i + 1e-12 h (likewise in y and z): a
 // vertex or face exactly on a grid line (lattice inputs) then has no tie; the
@@ -871,7 +871,7 @@ __global__ void __launch_bounds__(256) k_grid(GridArgs A) {
 
 // The normal deposit and, in the first n_large blocks (one wavefront each), the large kernel
 // over the clip's retry queue, so that the few slow cells next to halos overlap the bulk.  Held to two
-// wavefronts per SIMD: at 258 registers, one too few for them, the 2M/256^3 deposit takes 36.8 ms, not 22.3.
+// wavefronts per SIMD: at 258 registers, two too many for them, the 2M/256^3 deposit takes 36.8 ms, not 22.3.
 template <typename PT4>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k_grid_fused(GridArgs A) {
     extern __shared__ char smem[];
@@ -913,8 +913,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
 // The kernel is bound by VALU issue (about 15 planes of 8 FP64 operations a round of 64 rows, with
 // the rows of a small cell filling half the lanes) and the latency of a cell's loads.  500k cells on
 // 192^3 points took 3.00 ms with every candidate point tested against the neighbours one by one and
-// take 0.76 ms; 100k cells on 240 x 216 x 192 points (27 a voxel) took 8.4-10.5 ms in tiles of points
-// that shared a list of candidate particles and take 0.54 ms.
+// take 0.75 ms; 100k cells on 240 x 216 x 192 points (27 a voxel) took 8.4-10.5 ms in tiles of points
+// that shared a list of candidate particles and take 0.53 ms.
 #define VT_SAMPLE_DENSE 4096  // candidates of a tile above which it leaves the points to the cells
 #define VT_CLAIM_NBR 136    // faces staged per cell (the large clip kernel keeps no more)
 
